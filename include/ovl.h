@@ -538,18 +538,23 @@ int ovl_net_apply(const ovl_net* n, const ovl_gauge* u, const void* in, void* ou
 /* ovl_stencil_tune: mode 1 (default; OVL_TUNE=0 in the environment starts
  *   with 0) tunes each stencil configuration (precision, link format, extra
  *   epilogue vectors, batch size, parity mode, volume) at its first launch:
- *   every candidate shape is timed with HIP events on a scratch output in
- *   two rounds of one warm-up and three timed launches, and the first
- *   candidate within 2% of the fastest is kept.  Mode 0 uses the largest
- *   allowed KR (KR divides nrhs, KR <= 4, <= 2 for FP64) and 256 threads.
- *   Changing the mode clears the tuned table.  Launches inside a HIP graph
- *   capture never tune (they use the default until a tuned shape exists).
- *   Candidate shapes: (a) KR vectors per thread, one lattice pass per
- *   group of KR vectors, 128 or 256 threads; (b) the same with all
- *   nrhs/KR groups side by side in one workgroup (32 or 64 sites x groups
- *   threads, at most 512); (c) one-vector kernels that issue the loads of
- *   the next 1..3 directions before the arithmetic of the current one
- *   (pipeline depth 2..4); each in h order, in t-major order (blocks of a
+ *   candidate shapes are timed with HIP events on a scratch output in two
+ *   rounds of one warm-up and 3 timed launches (24 for batches below 8 MiB),
+ *   and the first candidate within 2% of the fastest is kept.  Mode 0 uses
+ *   the largest allowed KR (KR divides nrhs, KR <= 4, <= 2 for FP64) and 256
+ *   threads; block orders other than h order are tried for batches of at
+ *   least 4 MiB.  Changing the mode clears the tuned table.  Launches inside a
+ *   HIP graph capture never tune (they use the default until a tuned shape
+ *   exists).
+ *   Shapes: (a) 256 threads: the four directions of a tile of 64 sites on
+ *   the four waves of a workgroup, KR vectors per thread, partial sums
+ *   exchanged through LDS, one lattice pass per group of KR vectors; 128
+ *   threads: one site and all directions per thread (not a candidate of the
+ *   tuner); (b) one site and all directions per thread with all nrhs/KR
+ *   groups side by side in one workgroup (32 or 64 sites x groups threads,
+ *   at most 512); (c) pipeline depth 2..4: as (a) with 256 threads and
+ *   KR = 1, whatever the depth (every load of a wave's direction is in flight
+ *   at once); each in h order, in t-major order (blocks of a
  *   parity walk t for a fixed tile of the x-y-z half slice, so that
  *   t-neighbours come from cache) or in z-slab order (blocks cover a slab
  *   of tm = 4 or 8 z-planes at t, then the same slab at t + 1, ..., so a

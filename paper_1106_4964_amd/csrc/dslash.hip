@@ -49,22 +49,29 @@ bool tuning_enabled() {
   return m == 1;
 }
 
-std::vector<Shape> candidates(int prec, int nrhs, int Lz) {
+// The shapes that win somewhere (all shapes timed on 30 lattices, precisions
+// and batch sizes from 4^4 to 32^3x64): split directions (256 threads)
+// nearly everywhere, by 2-45%; the groups of vectors side by side in one
+// workgroup, which share their links through L1, for FP32 batches (12 rhs at
+// 24^3x64: 935 against 960 us, at 16^3x32: 125 against 134 us).  One
+// direction after the other with a group per block (128 threads) loses
+// everywhere (F16, 12 rhs at 24^3x64: 520 against 469 us; 4^4 FP64: 6.3
+// against 4.2 us) and is only run when pinned.
+std::vector<Shape> candidates(int prec, int nrhs, int Lz, size_t batch_bytes) {
   std::vector<Shape> c;
   const int kmax = prec == OVL_F64 ? 2 : 4;
-  // block orders: by h, t-major, and z-slabs of 4 and 8 planes
+  // block orders: by h and, for batches that do not fit an XCD's 4 MB L2
+  // (below, the order moves the time by 2-3% at most), t-major and z-slabs
+  // of 4 and 8 planes
   for (int tm : {0, 1, 4, 8}) {
-    if (tm > Lz) continue;
+    if (tm > Lz || (tm > 0 && batch_bytes < (size_t(4) << 20))) continue;
     for (int kr = 1; kr <= kmax; ++kr)
       if (nrhs % kr == 0) {
-        for (int bs : {128, 256}) c.push_back({kr, bs, 0, 0, tm});
-        if (nrhs > kr)  // several groups: try them side by side in one workgroup
+        c.push_back({kr, 256, 0, 0, tm});
+        if (nrhs > kr && kr < 4)  // several groups: try them side by side in one workgroup
           for (int bs : {32, 64})
             if (bs * (nrhs / kr) <= 512) c.push_back({kr, bs, 0, 1, tm});
       }
-    for (int dep : {2, 3, 4})
-      if (prec != OVL_F64 || dep == 2)
-        for (int bs : {128, 256}) c.push_back({1, bs, dep, 0, tm});
   }
   return c;
 }
@@ -94,22 +101,24 @@ Shape pick_shape(const StencilArgs& A, int prec, int recon, int nrhs, hipStream_
   hipEvent_t e0, e1;
   OVL_HIP(hipEventCreate(&e0));
   OVL_HIP(hipEventCreate(&e1));
-  // two rounds over the candidates, each timed over 3 launches after a
+  // two rounds over the candidates, each timed over 3 launches (24 where a
+  // launch takes a few microseconds, which events resolve poorly) after a
   // warm-up launch; a candidate's time is its better round.  The first
   // candidate (in list order) within 2% of the fastest wins, so that shapes
   // that time alike give the same choice from run to run.
-  const std::vector<Shape> cand = candidates(prec, nrhs, A.g.Lz);
+  const std::vector<Shape> cand = candidates(prec, nrhs, A.g.Lz, A.vstride * nrhs);
   std::vector<float> best_ms(cand.size(), 1e30f);
+  const int reps = A.vstride * nrhs < (size_t(8) << 20) ? 24 : 3;
   for (int round = 0; round < 2; ++round)
     for (size_t i = 0; i < cand.size(); ++i) {
       launch_shape(T, prec, recon, nrhs, cand[i], s);  // warm-up
       OVL_HIP(hipEventRecord(e0, s));
-      for (int r = 0; r < 3; ++r) launch_shape(T, prec, recon, nrhs, cand[i], s);
+      for (int r = 0; r < reps; ++r) launch_shape(T, prec, recon, nrhs, cand[i], s);
       OVL_HIP(hipEventRecord(e1, s));
       OVL_HIP(hipEventSynchronize(e1));
       float ms = 0.f;
       OVL_HIP(hipEventElapsedTime(&ms, e0, e1));
-      best_ms[i] = std::min(best_ms[i], ms);
+      best_ms[i] = std::min(best_ms[i], ms / reps);
     }
   float fastest = 1e30f;
   for (float t : best_ms) fastest = std::min(fastest, t);

@@ -177,6 +177,9 @@ Geo make_geo(const int* d) {
   g.sz = g.lxh * d[1];
   g.st = g.lxh * d[1] * d[2];
   g.Nh = g.st * d[3];
+  g.dx = make_fastdiv(g.lxh);
+  g.dy = make_fastdiv(g.Ly);
+  g.dz = make_fastdiv(g.Lz);
   return g;
 }
 

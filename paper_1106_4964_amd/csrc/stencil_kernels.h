@@ -3,12 +3,13 @@
 // precision and link format is instantiated in a translation unit of its own
 // (stencil_<prec>.hip), so the kernels compile in parallel.
 //
-// One thread computes the 12 complex output components of one site for KR
-// right-hand sides.  For each of the 8 directions it loads the neighbour
-// spinor, spin-projects it to a 2x3 half spinor with (1 -+ gamma_mu),
-// multiplies both colour vectors by U_mu(x) or U_mu(x-mu)^dag and adds the
-// result back, the lower two spin components being fixed multiples of the
-// upper two (chiral basis).  The epilogue forms
+// For each of the 8 directions the neighbour spinor is loaded, spin-projected
+// to a 2x3 half spinor with (1 -+ gamma_mu), both colour vectors are
+// multiplied by U_mu(x) or U_mu(x-mu)^dag and the result is added back, the
+// lower two spin components being fixed multiples of the upper two (chiral
+// basis).  stencil_split_kernel shares a site between four threads, one per
+// direction; stencil_kernel does a site's 8 hops in one thread.  Both treat
+// KR right-hand sides per thread.  The epilogue forms
 // G(a*in + b*hop) + sum_j c_j G_j(v_j) at the output site, which covers
 // D_w(m), H_w = gamma5 D_w(-rho), and the Clenshaw update of the polynomial
 // sign function (Sec. V) in one pass.
@@ -20,8 +21,8 @@ namespace ovl {
 
 struct Shape {
   int kr;    // vectors per thread
-  int bs;    // threads per block (sites per block when rin)
-  int pipe;  // 0: plain kernel; >= 2: pipelined one-vector kernel of that depth
+  int bs;    // threads per block (sites per block when rin); 256 = split directions
+  int pipe;  // >= 2: split directions, one vector per thread (one kernel for every depth: all its loads are in flight)
   int rin;   // 1: the nrhs/kr vector groups are the y-dimension of the block
   int tm;    // block order (StencilArgs::tmaj): 0 by h, 1 t-major, >= 2 z-slabs of tm planes
 };
@@ -117,33 +118,25 @@ __device__ inline void cmac(T& re, T& im, Cx<T> u, Cx<T> h) {
   }
 }
 
-// sum_b u_b h_b (CONJ: conj(u_b) h_b).  CHAIN: one FMA chain per real part
-// (4 instructions per complex multiply-add); otherwise products summed as a
-// tree (6 instructions, shorter dependence chains, fewer live registers).
-template <bool CONJ, bool CHAIN, typename T>
+// sum_b u_b h_b (CONJ: conj(u_b) h_b), one FMA chain per real part (4
+// instructions per complex multiply-add).
+template <bool CONJ, typename T>
 __device__ inline Cx<T> row3(Cx<T> u0, Cx<T> u1, Cx<T> u2, const Cx<T>* h) {
-  if constexpr (CHAIN) {
-    T re = T(0), im = T(0);
-    cmac<CONJ>(re, im, u0, h[0]);
-    cmac<CONJ>(re, im, u1, h[1]);
-    cmac<CONJ>(re, im, u2, h[2]);
-    return {re, im};
-  } else if constexpr (CONJ) {
-    return cmul_conj(u0, h[0]) + cmul_conj(u1, h[1]) + cmul_conj(u2, h[2]);
-  } else {
-    return u0 * h[0] + u1 * h[1] + u2 * h[2];
-  }
+  T re = T(0), im = T(0);
+  cmac<CONJ>(re, im, u0, h[0]);
+  cmac<CONJ>(re, im, u1, h[1]);
+  cmac<CONJ>(re, im, u2, h[2]);
+  return {re, im};
 }
 
 // w[s] = U h[s]  (DAG = false)  or  U^dag h[s]  (DAG = true)
-template <bool DAG, bool CHAIN, typename T>
+template <bool DAG, typename T>
 __device__ inline void colour_mul(const Cx<T> (*u)[3], const Cx<T> (*h)[3], Cx<T> (*w)[3]) {
 #pragma unroll
   for (int s = 0; s < 2; ++s)
 #pragma unroll
     for (int a = 0; a < 3; ++a)
-      w[s][a] = DAG ? row3<true, CHAIN>(u[0][a], u[1][a], u[2][a], h[s])
-                    : row3<false, CHAIN>(u[a][0], u[a][1], u[a][2], h[s]);
+      w[s][a] = DAG ? row3<true>(u[0][a], u[1][a], u[2][a], h[s]) : row3<false>(u[a][0], u[a][1], u[a][2], h[s]);
 }
 
 // ------------------------------------------------------- F16 operands
@@ -213,12 +206,6 @@ __device__ inline uint32_t raw_word(const SpinorRaw<OVL_F16>& r, int c) {
   return k == 0 ? v.x : k == 1 ? v.y : k == 2 ? v.z : v.w;
 }
 
-// One FMA chain per real part of each colour row.
-template <int P, int NV>
-constexpr bool chain_form() {
-  return true;
-}
-
 // F16 links are converted to f32 once per thread and then hidden from the
 // optimiser: otherwise it folds the conversions into the colour products as
 // v_fma_mix_f32, which issues at about 70% of the rate of v_fma_f32
@@ -234,7 +221,7 @@ __device__ inline void opaque_link(Cx<typename Prec<P>::real> (*u)[3]) {
   }
 }
 
-template <int P, int R, int MU, int KR, bool CH>
+template <int P, int R, int MU, int KR>
 __device__ inline void hop_dir(const StencilArgs& A, const char* in, int p, int h, const int* nb,
                                Cx<typename Prec<P>::real> (*acc)[12], typename Prec<P>::real bu,
                                typename Prec<P>::real bl) {
@@ -258,7 +245,7 @@ __device__ inline void hop_dir(const StencilArgs& A, const char* in, int p, int 
       SpinorIO<P>::load(in + k * A.vstride, q, nb[MU], A.g.Nh, s);
       project<MU, -1>(s, hs);
     }
-    colour_mul<false, CH>(u, hs, w);
+    colour_mul<false>(u, hs, w);
     accumulate<MU, -1>(acc[k], w, bu, bl);
   }
   // backward: U_mu(x - mu)^dag (1 + gamma_mu) in(x - mu)
@@ -278,7 +265,7 @@ __device__ inline void hop_dir(const StencilArgs& A, const char* in, int p, int 
       SpinorIO<P>::load(in + k * A.vstride, q, nb[MU + 4], A.g.Nh, s);
       project<MU, +1>(s, hs);
     }
-    colour_mul<true, CH>(u, hs, w);
+    colour_mul<true>(u, hs, w);
     accumulate<MU, +1>(acc[k], w, bu, bl);
   }
 }
@@ -411,118 +398,314 @@ __global__ __launch_bounds__(RIN ? 512 : 256) void stencil_kernel(StencilArgs A)
     for (int c = 0; c < 12; ++c) acc[k][c] = {real(0), real(0)};
   real bu, bl;
   hop_weights(A, bu, bl);
-  hop_dir<P, R, 0, KR, chain_form<P, NV>()>(A, in, p, h, nb, acc, bu, bl);
-  hop_dir<P, R, 1, KR, chain_form<P, NV>()>(A, in, p, h, nb, acc, bu, bl);
-  hop_dir<P, R, 2, KR, chain_form<P, NV>()>(A, in, p, h, nb, acc, bu, bl);
-  hop_dir<P, R, 3, KR, chain_form<P, NV>()>(A, in, p, h, nb, acc, bu, bl);
+  hop_dir<P, R, 0, KR>(A, in, p, h, nb, acc, bu, bl);
+  hop_dir<P, R, 1, KR>(A, in, p, h, nb, acc, bu, bl);
+  hop_dir<P, R, 2, KR>(A, in, p, h, nb, acc, bu, bl);
+  hop_dir<P, R, 3, KR>(A, in, p, h, nb, acc, bu, bl);
 
 #pragma unroll
   for (int k = 0; k < KR; ++k) epilogue<P, NV>(A, voff + k * A.vstride, p, h, acc[k]);
 }
 
-// Software-pipelined variant for one vector per thread: the raw loads of
-// direction D + DEP - 1 are issued before the arithmetic of direction D, so
-// DEP directions' worth of loads are in flight per wave.  Directions run
-// +x, -x, +y, -y, ... (D = 2 mu + backward).
-template <int P, int R, int D>
-__device__ inline void pipe_issue(const StencilArgs& A, const char* in, int p, int h, const int* nb,
-                                  SpinorRaw<P>& sr, LinkRaw<P, R>& lr) {
-  constexpr int MU = D / 2;
-  const int q = 1 - p;
-  if constexpr (D % 2 == 0) {
-    spinor_load_raw<P>(in, q, nb[MU], A.g.Nh, sr);
-    link_load_raw<P, R>(A.links, MU, p, h, A.g.Nh, lr);
+// ------------------------------------------------------- split directions
+// One workgroup of four waves per tile of 64 sites: wave w computes the two
+// hops of direction mu = w for KR vectors of every site, and the four partial
+// sums meet in LDS (one vector at a time, 24 KB in FP32), where the vector's
+// 16-byte output blocks are dealt out over the waves for the epilogue.
+//
+// Against one thread per site and all directions:
+//  - all loads of a wave (two links, 2 KR spinors) are requested before the
+//    first use, so it waits for memory once instead of once per direction;
+//    small lattices have four times the waves.  4^4 FP64: 6.3 -> 4.2 us a
+//    launch; 8^3x16 F16, 12 rhs: 10.1 -> 7.4 us; 16^3x32 F16, 1 rhs: 10.3 ->
+//    9.2 us, FP64: 33.9 -> 32.3 us.
+//  - a quarter of the sites in flight per XCD, so that neighbours and links
+//    are found in its L2: 24^3x64 F16, 12 rhs, no extra vectors: 1.10 ->
+//    0.53 million KiB FETCH_SIZE a launch.
+//  - the two hops of a direction share the addition (split_hop).
+// 24^3x64 (H_w / Clenshaw step with three extra vectors, us): F16 12 rhs
+// 435 / 635 -> 395 / 600, FP32-12 1 rhs 85 / 115 -> 76 / 110, FP64 1 rhs
+// 228 / 304 -> 214 / 299, FP64 12 rhs 1988 (start) -> 1800.
+// What bounds it there: with three extra vectors HBM (3.1 GB at 5.2 TB/s);
+// without, the reads between L1 and L2 (34 million 128-byte requests in 0.4 ms
+// for F16, 11 TB/s; 93 million in 0.88 ms for FP32, 13 TB/s) and the FP32
+// instructions (1120 a site and vector, about 70% of the issue rate).
+//
+// Uniform base + 32-bit lane offset for every load, so that the address
+// arithmetic stays in scalar registers.
+template <int P>
+__device__ inline void raw_spinor_at(const char* base, uint32_t off, int Nh, SpinorRaw<P>& r) {
+#pragma unroll
+  for (int j = 0; j < 12 / Prec<P>::cpb; ++j)
+    r.b[j] = *reinterpret_cast<const uint4*>(base + static_cast<size_t>(j) * Nh * 16 + off);
+}
+
+template <int P, int R>
+__device__ inline void raw_link_at(const char* base, uint32_t h, int Nh, LinkRaw<P, R>& r) {
+  using F = LinkFmt<P, R>;
+#pragma unroll
+  for (int k = 0; k < F::K; ++k)
+    __builtin_memcpy(&r.w[k * F::E / 4],
+                     __builtin_assume_aligned(base + static_cast<size_t>(k) * Nh * F::E + h * F::E, F::E), F::E);
+}
+
+// The 3x3 link from raw data.  F16: converted once per link and hidden from
+// the optimiser (see opaque_link) before row 2 is rebuilt, so that the
+// rebuild runs in v_fma_f32 as well.
+template <int P, int R>
+__device__ inline void raw_link_unpack(const LinkRaw<P, R>& r, Cx<typename Prec<P>::real> (*u)[3]) {
+  if constexpr (P == OVL_F16 && R == 12) {
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+      u[k / 3][k % 3] = ScalarIO<P>::load1(reinterpret_cast<const char*>(&r.w[k]));
+      asm("" : "+v"(u[k / 3][k % 3].re), "+v"(u[k / 3][k % 3].im));
+    }
+    reconstruct_row2(u);
   } else {
-    spinor_load_raw<P>(in, q, nb[MU + 4], A.g.Nh, sr);
-    link_load_raw<P, R>(A.links, MU, q, nb[MU + 4], A.g.Nh, lr);
+    link_unpack<P, R>(r, u);
+    opaque_link<P>(u);
   }
 }
 
-template <int P, int R, int D>
-__device__ inline void pipe_consume(const SpinorRaw<P>& sr, const LinkRaw<P, R>& lr, Cx<typename Prec<P>::real>* acc,
-                                    typename Prec<P>::real bu, typename Prec<P>::real bl) {
-  using real = typename Prec<P>::real;
-  constexpr int MU = D / 2;
-  constexpr bool CH = P != OVL_F16;  // the pipelined kernels keep the pairwise form for FP16
-  Cx<real> hs[2][3], w[2][3], u[3][3];
-  link_unpack<P, R>(lr, u);
-  opaque_link<P>(u);
+// Half spinor of direction MU (SGN -1: forward, +1: backward) from raw data.
+template <int P, int MU, int SGN>
+__device__ inline void raw_project(const SpinorRaw<P>& sr, Cx<typename Prec<P>::real> (*hs)[3]) {
   if constexpr (P == OVL_F16) {
     uint32_t sw[12];
 #pragma unroll
     for (int c = 0; c < 12; ++c) sw[c] = raw_word(sr, c);
-    if constexpr (D % 2 == 0) project_f16<MU, -1>(sw, hs);
-    else project_f16<MU, +1>(sw, hs);
+    project_f16<MU, SGN>(sw, hs);
   } else {
-    Cx<real> s[12];
+    Cx<typename Prec<P>::real> s[12];
     spinor_unpack<P>(sr, s);
-    if constexpr (D % 2 == 0) project<MU, -1>(s, hs);
-    else project<MU, +1>(s, hs);
-  }
-  if constexpr (D % 2 == 0) {
-    colour_mul<false, CH>(u, hs, w);
-    accumulate<MU, -1>(acc, w, bu, bl);
-  } else {
-    colour_mul<true, CH>(u, hs, w);
-    accumulate<MU, +1>(acc, w, bu, bl);
+    project<MU, SGN>(s, hs);
   }
 }
 
-template <int P, int R, int DEP, int D>
-__device__ inline void pipe_run(const StencilArgs& A, const char* in, int p, int h, const int* nb,
-                                SpinorRaw<P> (&sr)[DEP], LinkRaw<P, R> (&lr)[DEP],
-                                Cx<typename Prec<P>::real>* acc, typename Prec<P>::real bu,
-                                typename Prec<P>::real bl) {
-  if constexpr (D + DEP - 1 < 8) pipe_issue<P, R, D + DEP - 1>(A, in, p, h, nb, sr[(D + DEP - 1) % DEP], lr[(D + DEP - 1) % DEP]);
-  pipe_consume<P, R, D>(sr[D % DEP], lr[D % DEP], acc, bu, bl);
-  if constexpr (D + 1 < 8) pipe_run<P, R, DEP, D + 1>(A, in, p, h, nb, sr, lr, acc, bu, bl);
+// ph * (s - 2 f) for the phase ph coded as in proj1.
+template <int PH, typename T>
+__device__ inline Cx<T> phase_diff(Cx<T> s, Cx<T> f) {
+  const T two = T(2);
+  if constexpr (PH == 0) return {ffma(-two, f.re, s.re), ffma(-two, f.im, s.im)};
+  else if constexpr (PH == 1) return {ffma(two, f.re, -s.re), ffma(two, f.im, -s.im)};
+  else if constexpr (PH == 2) return {ffma(two, f.im, -s.im), ffma(-two, f.re, s.re)};
+  else return {ffma(-two, f.im, s.im), ffma(two, f.re, -s.re)};
 }
 
-template <int P, int R, int DEP, int D>
-__device__ inline void pipe_prologue(const StencilArgs& A, const char* in, int p, int h, const int* nb,
-                                     SpinorRaw<P> (&sr)[DEP], LinkRaw<P, R> (&lr)[DEP]) {
-  if constexpr (D < DEP - 1) {
-    pipe_issue<P, R, D>(A, in, p, h, nb, sr[D], lr[D]);
-    pipe_prologue<P, R, DEP, D + 1>(A, in, p, h, nb, sr, lr);
-  }
-}
-
-template <int P, int R, int NV, int DEP>
-__global__ __launch_bounds__(256) void stencil_pipe_kernel(StencilArgs A) {
+// Both hops of direction MU for KR vectors, val[k] = the 12 components of
+// U_mu(x)(1 - gamma_mu) in(x+mu) + U_mu(x-mu)^dag (1 + gamma_mu) in(x-mu).
+// With f and g the two transported half spinors, the upper spins are f + g
+// (g's colour products are accumulated onto f) and the lower spins a phase
+// times g - f = (f + g) - 2 f: 12 instructions where adding the two hops one
+// after the other takes 48.
+template <int P, int R, int MU, int KR>
+__device__ inline void split_hop(const StencilArgs& A, const char* in, int p, int h, int x, int y, int z, int t,
+                                 Cx<typename Prec<P>::real> (*val)[12]) {
   using real = typename Prec<P>::real;
-  const Geo& g = A.g;
-  int p, h;
-  if (!stencil_site(A, p, h)) return;
-  const size_t voff = static_cast<size_t>(blockIdx.y) * A.vstride;
-  const char* in = static_cast<const char*>(A.in) + voff;
-  int x, y, z, t, nb[8];
-  site_coords(g, p, h, x, y, z, t);
-  site_neighbors(g, h, x, y, z, t, nb);
-  SpinorRaw<P> sr[DEP];
-  LinkRaw<P, R> lr[DEP];
-  pipe_prologue<P, R, DEP, 0>(A, in, p, h, nb, sr, lr);
-  Cx<real> acc[12];
+  using LF = LinkFmt<P, R>;
+  const int Nh = A.g.Nh, q = 1 - p;
+  int nb[8];
+  site_neighbors(A.g, h, x, y, z, t, nb);
+  const uint32_t hf = static_cast<uint32_t>(nb[MU]), hb = static_cast<uint32_t>(nb[MU + 4]);
+  const char* src = in + static_cast<size_t>(q) * (12 / Prec<P>::cpb) * Nh * 16;
+  const char* lk = static_cast<const char*>(A.links) + static_cast<size_t>(MU) * 2 * LF::K * Nh * LF::E;
+  const size_t lpar = static_cast<size_t>(LF::K) * Nh * LF::E;
+  SpinorRaw<P> sf[KR], sb[KR];
+  LinkRaw<P, R> lf, lb;
+  raw_link_at<P, R>(lk + p * lpar, static_cast<uint32_t>(h), Nh, lf);
 #pragma unroll
-  for (int c = 0; c < 12; ++c) acc[c] = {real(0), real(0)};
+  for (int k = 0; k < KR; ++k) raw_spinor_at<P>(src + k * A.vstride, hf * 16u, Nh, sf[k]);
+  auto load_back = [&] {
+    raw_link_at<P, R>(lk + q * lpar, hb, Nh, lb);
+#pragma unroll
+    for (int k = 0; k < KR; ++k) raw_spinor_at<P>(src + k * A.vstride, hb * 16u, Nh, sb[k]);
+  };
+  // both hops' operands in flight at once while they fit the registers
+  constexpr bool ahead = 2 * (sizeof(SpinorRaw<P>) * KR + sizeof(LinkRaw<P, R>)) <= 680;
+  if constexpr (ahead) {
+    load_back();
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  Cx<real> u[3][3], f[KR][2][3];
+  raw_link_unpack<P, R>(lf, u);
+#pragma unroll
+  for (int k = 0; k < KR; ++k) {
+    Cx<real> hs[2][3];
+    raw_project<P, MU, -1>(sf[k], hs);
+    colour_mul<false>(u, hs, f[k]);
+  }
+  if constexpr (ahead) __builtin_amdgcn_sched_barrier(0);
+  if constexpr (!ahead) load_back();
+  raw_link_unpack<P, R>(lb, u);
+  constexpr int l0 = MU == 0 ? 2 : MU == 1 ? 0 : MU == 2 ? 2 : 0;
+  constexpr int l1 = MU == 0 ? 2 : MU == 1 ? 1 : MU == 2 ? 3 : 0;
+  constexpr int s0 = MU < 2 ? 1 : 0, s1 = MU < 2 ? 0 : 1;
+#pragma unroll
+  for (int k = 0; k < KR; ++k) {
+    Cx<real> hs[2][3];
+    raw_project<P, MU, +1>(sb[k], hs);
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        real re = f[k][s][a].re, im = f[k][s][a].im;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) cmac<true>(re, im, u[c][a], hs[s][c]);
+        val[k][3 * s + a] = {re, im};
+      }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      val[k][6 + c] = phase_diff<l0>(val[k][3 * s0 + c], f[k][s0][c]);
+      val[k][9 + c] = phase_diff<l1>(val[k][3 * s1 + c], f[k][s1][c]);
+    }
+  }
+}
+
+// Epilogue of one 16-byte output block u (components u*cpb ...): a = the sum
+// of the hops, rin and rv the same block of the input and the extra vectors.
+template <int P, int NV>
+__device__ inline void split_block(const StencilArgs& A, size_t off, int u, const u32x4_t& rin, const u32x4_t* rv,
+                                   Cx<typename Prec<P>::real>* a) {
+  using real = typename Prec<P>::real;
+  constexpr int cpb = Prec<P>::cpb;
   real bu, bl;
   hop_weights(A, bu, bl);
-  pipe_run<P, R, DEP, 0>(A, in, p, h, nb, sr, lr, acc, bu, bl);
-  epilogue<P, NV>(A, voff, p, h, acc);
+#pragma unroll
+  for (int j = 0; j < cpb; ++j) a[j] = (u * cpb + j >= 6 ? bl : bu) * a[j];
+#pragma unroll
+  for (int q = 0; q <= NV; ++q) {
+    const u32x4_t raw = q == 0 ? rin : rv[q == 0 ? 0 : q - 1];
+    const real cu = static_cast<real>(q == 0 ? A.a : A.cv[q == 0 ? 0 : q - 1]);
+    const real cl = (q == 0 ? A.g5 != 0 : ((A.g5v >> (q == 0 ? 0 : q - 1)) & 1) != 0) ? -cu : cu;
+    if constexpr (P == OVL_F16) {
+      const uint32_t wd[4] = {raw.x, raw.y, raw.z, raw.w};
+#pragma unroll
+      for (int j = 0; j < cpb; ++j) {
+        const float s = u * cpb + j >= 6 ? cl : cu;
+        a[j] = {mix_fma<0>(wd[j], s, a[j].re), mix_fma<1>(wd[j], s, a[j].im)};
+      }
+    } else {
+      Cx<real> x[cpb];
+      Block<P>::load(&raw, x);
+#pragma unroll
+      for (int j = 0; j < cpb; ++j) addph<0>(a[j], x[j], u * cpb + j >= 6 ? cl : cu);
+    }
+  }
+  u32x4_t v;
+  Block<P>::store(&v, a);
+  __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t*>(static_cast<char*>(A.out) + off));
 }
 
+template <int P, int R, int NV, int KR>
+__global__ __launch_bounds__(256) void stencil_split_kernel(StencilArgs A) {
+  using real = typename Prec<P>::real;
+  constexpr int cpb = Prec<P>::cpb, NB = 12 / cpb;
+  constexpr int CH = 24 * sizeof(real) / 16, CPU = CH / NB;  // 16-byte chunks per vector and per output block
+  constexpr int UW = (NB + 3) / 4;                           // output blocks per wave and vector
+  __shared__ u32x4_t part[4][CH][64];
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const Geo& g = A.g;
+  int p, h;
+  const bool ok = tile_site(A, xcd_remap(blockIdx.x, gridDim.x), 64, lane, p, h);
+  if (!ok) h = 0;  // lanes past the end compute site 0 and store nothing
+  const size_t voff = static_cast<size_t>(blockIdx.y) * KR * A.vstride;
+  const char* in = static_cast<const char*>(A.in) + voff;
+  int x, y, z, t;
+  site_coords(g, p, h, x, y, z, t);
+  Cx<real> val[KR][12];
+  switch (w) {
+    case 0: split_hop<P, R, 0, KR>(A, in, p, h, x, y, z, t, val); break;
+    case 1: split_hop<P, R, 1, KR>(A, in, p, h, x, y, z, t, val); break;
+    case 2: split_hop<P, R, 2, KR>(A, in, p, h, x, y, z, t, val); break;
+    default: split_hop<P, R, 3, KR>(A, in, p, h, x, y, z, t, val); break;
+  }
+
+  // Output blocks of this wave: block 4 i + (w + k) % 4 of vector k.  The
+  // epilogue's operands are requested here, before the exchange: requested
+  // with the hops' operands they cost registers the hops need (F16, 12 rhs,
+  // 24^3x64, three extra vectors: 692 us against 596), and vector by vector
+  // they cost one memory latency each.
+  u32x4_t rin[KR][UW], rv[KR][UW][NV == 0 ? 1 : NV];
+  const uint32_t hoff = static_cast<uint32_t>(h) * 16u;
+  auto block_off = [&](int k, int u) {
+    return voff + k * A.vstride + (static_cast<size_t>(p) * NB + u) * g.Nh * 16;
+  };
+#pragma unroll
+  for (int k = 0; k < KR; ++k)
+#pragma unroll
+    for (int i = 0; i < UW; ++i) {
+      const int u = 4 * i + ((w + k) & 3);
+      if (u < NB) {
+        const size_t off = block_off(k, u);
+        rin[k][i] = *reinterpret_cast<const u32x4_t*>(static_cast<const char*>(A.in) + off + hoff);
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+          rv[k][i][j] = __builtin_nontemporal_load(
+              reinterpret_cast<const u32x4_t*>(static_cast<const char*>(A.v[j]) + off + hoff));
+      }
+    }
+
+#pragma unroll
+  for (int k = 0; k < KR; ++k) {
+    if (k > 0) __syncthreads();
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      u32x4_t v;
+      __builtin_memcpy(&v, reinterpret_cast<const char*>(val[k]) + 16 * c, 16);
+      part[w][c][lane] = v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < UW; ++i) {
+      const int u = 4 * i + ((w + k) & 3);
+      if (u < NB && ok) {
+        Cx<real> a[cpb];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          Cx<real> b[cpb];
+#pragma unroll
+          for (int c = 0; c < CPU; ++c) {
+            const u32x4_t v = part[s][u * CPU + c][lane];
+            __builtin_memcpy(reinterpret_cast<char*>(b) + 16 * c, &v, 16);
+          }
+#pragma unroll
+          for (int j = 0; j < cpb; ++j) a[j] = s == 0 ? b[j] : a[j] + b[j];
+        }
+        split_block<P, NV>(A, block_off(k, u) + hoff, u, rin[k][i], rv[k][i], a);
+      }
+    }
+  }
+}
 
 template <int P, int R, int NV>
 void launch_k(const StencilArgs& A0, int nrhs, Shape sh, hipStream_t s) {
   StencilArgs A = A0;
   A.tmaj = sh.tm;
+  const bool split = sh.pipe || (sh.bs == 256 && !sh.rin);
+  const int sites = split ? 64 : sh.bs;  // per block
   int hblocks;
   if (sh.tm >= 2) {
     OVL_REQUIRE(sh.tm <= A.g.Lz, OVL_E_ARG, "stencil: slab thicker than the lattice");
-    hblocks = ((A.g.Lz + sh.tm - 1) / sh.tm) * A.g.Lt * ((sh.tm * A.g.sz + sh.bs - 1) / sh.bs);
+    hblocks = ((A.g.Lz + sh.tm - 1) / sh.tm) * A.g.Lt * ((sh.tm * A.g.sz + sites - 1) / sites);
   } else if (sh.tm == 1) {
-    hblocks = ((A.g.st + sh.bs - 1) / sh.bs) * A.g.Lt;
+    hblocks = ((A.g.st + sites - 1) / sites) * A.g.Lt;
   } else {
-    hblocks = (A.g.Nh + sh.bs - 1) / sh.bs;
+    hblocks = (A.g.Nh + sites - 1) / sites;
+  }
+  if (split) {
+    dim3 grid(hblocks * A.npar, nrhs / sh.kr), block(256);
+    switch (sh.kr) {
+      case 1: hipLaunchKernelGGL((stencil_split_kernel<P, R, NV, 1>), grid, block, 0, s, A); break;
+      case 2: hipLaunchKernelGGL((stencil_split_kernel<P, R, NV, 2>), grid, block, 0, s, A); break;
+      case 3:
+        if constexpr (P != OVL_F64) hipLaunchKernelGGL((stencil_split_kernel<P, R, NV, 3>), grid, block, 0, s, A);
+        break;
+      case 4:
+        if constexpr (P != OVL_F64) hipLaunchKernelGGL((stencil_split_kernel<P, R, NV, 4>), grid, block, 0, s, A);
+        break;
+      default: throw Error(OVL_E_ARG, "stencil: unsupported vectors per thread");
+    }
+    return;
   }
   if (sh.rin) {
     const int groups = nrhs / sh.kr;
@@ -538,15 +721,6 @@ void launch_k(const StencilArgs& A0, int nrhs, Shape sh, hipStream_t s) {
     return;
   }
   dim3 grid(hblocks * A.npar, nrhs / sh.kr), block(sh.bs);
-  if (sh.pipe) {
-    switch (sh.pipe) {
-      case 2: hipLaunchKernelGGL((stencil_pipe_kernel<P, R, NV, 2>), grid, block, 0, s, A); break;
-      case 3: hipLaunchKernelGGL((stencil_pipe_kernel<P, R, NV, 3>), grid, block, 0, s, A); break;
-      case 4: hipLaunchKernelGGL((stencil_pipe_kernel<P, R, NV, 4>), grid, block, 0, s, A); break;
-      default: throw Error(OVL_E_ARG, "stencil: unsupported pipeline depth");
-    }
-    return;
-  }
   switch (sh.kr) {
     case 1: hipLaunchKernelGGL((stencil_kernel<P, R, NV, 1, false>), grid, block, 0, s, A); break;
     case 2: hipLaunchKernelGGL((stencil_kernel<P, R, NV, 2, false>), grid, block, 0, s, A); break;

@@ -247,3 +247,46 @@ def test_mem_stats_counts_links():
     ovl.ovl_mem_stats(ctypes.byref(live), ctypes.byref(peak), 0)
     assert live.value == live0
     assert peak.value >= live0 + links
+
+
+@pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (2, 4, 6, 2), (4, 4, 4, 4), (10, 6, 6, 4)])
+def test_split_directions_kernel(prec, dims):
+    """The direction-split stencil (256 threads, tiles of 64 sites) where a tile
+    is larger than a parity (2^4: 8 sites), where tiles are whole (4^4: 128)
+    and ragged, at an x extent of 2 (one half-site per row), in h order and in
+    ragged z-slabs, for every number of vectors per thread, 18 and 12 reals,
+    one parity and both, against the oracle; D(m) of a low-order polynomial
+    (0 to 3 extra vectors) against the one-thread-per-site kernel."""
+    lat = Lattice(dims)
+    U = si.gauge_field(dims, 0.3, 11)
+    g = ovl.Geometry(dims)
+    psi = np.stack([si.gaussian_spinor(dims, 700 + r) for r in range(4)])
+    u = gu.UNIT_ROUNDOFF[prec]
+    full = [dirac.wilson_dslash(lat, U, p, 0.1) for p in psi]
+    odd = [dirac.wilson_dslash_parity(lat, U, p, 0.1, 1) for p in psi]
+    sgn = ovl.Sign(0.4, 7.0, n=4)
+    for c12 in (0, 1):
+        gauge = gu.make_gauge(g, U, [(prec, c12)])
+        for nrhs, kr in ((1, 1), (2, 2), (3, 3), (4, 4), (4, 2)):
+            if prec == ovl.OVL_F64 and kr > 2:
+                continue
+            inp = gu.pack(g, psi[:nrhs], prec, nrhs)
+            for tm in (0, 1, min(4, dims[2])):
+                for nv in range(4):
+                    ovl.stencil_set_shape(g, prec, c12, nv, nrhs, (kr, 256, 0, 0, tm))
+                for par, want in ((2, full), (1, odd)):
+                    out = gu.pack(g, np.zeros_like(psi[:nrhs]), prec, nrhs)
+                    ovl.ovl_dslash(out, inp, gauge, 0.1, par, prec, nrhs, None)
+                    got = np.reshape(gu.unpack(g, out, prec, nrhs), psi[:nrhs].shape)
+                    tol = 1e-13 if prec == ovl.OVL_F64 else 16 * u + 4e-7
+                    assert gu.rel_err(got, np.stack(want[:nrhs])) < tol, (c12, nrhs, kr, tm, par)
+                res = []
+                for bs in (256, 128):
+                    for nv in range(4):
+                        ovl.stencil_set_shape(g, prec, c12, nv, nrhs, (kr, bs, 0, 0, tm))
+                    out = gu.empty_field(g, prec, nrhs)
+                    ovl.ovl_overlap_apply(out, inp, gauge, 1.4, 0.05, sgn, None, 0, prec, nrhs, None)
+                    res.append(gu.unpack(g, out, prec, nrhs))
+                # ten stages, each within a rounding of its output of the other kernel's
+                assert gu.rel_err(res[0], res[1]) < 20 * u, (c12, nrhs, kr, tm)
