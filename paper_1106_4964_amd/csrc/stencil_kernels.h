@@ -482,22 +482,23 @@ __device__ inline void raw_project(const SpinorRaw<P>& sr, Cx<typename Prec<P>::
   }
 }
 
-// ph * (s - 2 f) for the phase ph coded as in proj1.
+// ph * (a - m f) for the phase ph coded as in proj1; m = 1 or 2.
 template <int PH, typename T>
-__device__ inline Cx<T> phase_diff(Cx<T> s, Cx<T> f) {
-  const T two = T(2);
-  if constexpr (PH == 0) return {ffma(-two, f.re, s.re), ffma(-two, f.im, s.im)};
-  else if constexpr (PH == 1) return {ffma(two, f.re, -s.re), ffma(two, f.im, -s.im)};
-  else if constexpr (PH == 2) return {ffma(two, f.im, -s.im), ffma(-two, f.re, s.re)};
-  else return {ffma(-two, f.im, s.im), ffma(two, f.re, -s.re)};
+__device__ inline Cx<T> phase_diff(Cx<T> a, T m, Cx<T> f) {
+  if constexpr (PH == 0) return {ffma(-m, f.re, a.re), ffma(-m, f.im, a.im)};
+  else if constexpr (PH == 1) return {ffma(m, f.re, -a.re), ffma(m, f.im, -a.im)};
+  else if constexpr (PH == 2) return {ffma(m, f.im, -a.im), ffma(-m, f.re, a.re)};
+  else return {ffma(-m, f.im, a.im), ffma(m, f.re, -a.re)};
 }
 
 // Both hops of direction MU for KR vectors, val[k] = the 12 components of
 // U_mu(x)(1 - gamma_mu) in(x+mu) + U_mu(x-mu)^dag (1 + gamma_mu) in(x-mu).
-// With f and g the two transported half spinors, the upper spins are f + g
-// (g's colour products are accumulated onto f) and the lower spins a phase
-// times g - f = (f + g) - 2 f: 12 instructions where adding the two hops one
-// after the other takes 48.
+// With f and g the two transported half spinors, the upper spins are f + g and
+// the lower spins a phase times g - f: 24 instructions where adding the two
+// hops one after the other takes 48.  At 16-bit storage g's colour products
+// are accumulated onto f and g - f = (f + g) - 2 f, 12 instructions; in FP32
+// that raised the error of H_w against 64 bits from 5.96e-8 to 6.21e-8, so
+// there (and in FP64) both are rounded once from f and g.
 template <int P, int R, int MU, int KR>
 __device__ inline void split_hop(const StencilArgs& A, const char* in, int p, int h, int x, int y, int z, int t,
                                  Cx<typename Prec<P>::real> (*val)[12]) {
@@ -544,19 +545,31 @@ __device__ inline void split_hop(const StencilArgs& A, const char* in, int p, in
   for (int k = 0; k < KR; ++k) {
     Cx<real> hs[2][3];
     raw_project<P, MU, +1>(sb[k], hs);
+    if constexpr (P == OVL_F16 || P == OVL_BF16) {
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
+      for (int s = 0; s < 2; ++s)
 #pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        real re = f[k][s][a].re, im = f[k][s][a].im;
+        for (int a = 0; a < 3; ++a) {
+          real re = f[k][s][a].re, im = f[k][s][a].im;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) cmac<true>(re, im, u[c][a], hs[s][c]);
-        val[k][3 * s + a] = {re, im};
+          for (int c = 0; c < 3; ++c) cmac<true>(re, im, u[c][a], hs[s][c]);
+          val[k][3 * s + a] = {re, im};
+        }
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        val[k][6 + c] = phase_diff<l0>(val[k][3 * s0 + c], real(2), f[k][s0][c]);
+        val[k][9 + c] = phase_diff<l1>(val[k][3 * s1 + c], real(2), f[k][s1][c]);
       }
+    } else {
+      Cx<real> b[2][3];
+      colour_mul<true>(u, hs, b);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      val[k][6 + c] = phase_diff<l0>(val[k][3 * s0 + c], f[k][s0][c]);
-      val[k][9 + c] = phase_diff<l1>(val[k][3 * s1 + c], f[k][s1][c]);
+      for (int c = 0; c < 3; ++c) {
+        val[k][c] = f[k][0][c] + b[0][c];
+        val[k][3 + c] = f[k][1][c] + b[1][c];
+        val[k][6 + c] = phase_diff<l0>(b[s0][c], real(1), f[k][s0][c]);
+        val[k][9 + c] = phase_diff<l1>(b[s1][c], real(1), f[k][s1][c]);
+      }
     }
   }
 }
@@ -659,18 +672,16 @@ __global__ __launch_bounds__(256) void stencil_split_kernel(StencilArgs A) {
     for (int i = 0; i < UW; ++i) {
       const int u = 4 * i + ((w + k) & 3);
       if (u < NB && ok) {
-        Cx<real> a[cpb];
+        Cx<real> b[4][cpb], a[cpb];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          Cx<real> b[cpb];
+        for (int s = 0; s < 4; ++s)
 #pragma unroll
           for (int c = 0; c < CPU; ++c) {
             const u32x4_t v = part[s][u * CPU + c][lane];
-            __builtin_memcpy(reinterpret_cast<char*>(b) + 16 * c, &v, 16);
+            __builtin_memcpy(reinterpret_cast<char*>(b[s]) + 16 * c, &v, 16);
           }
 #pragma unroll
-          for (int j = 0; j < cpb; ++j) a[j] = s == 0 ? b[j] : a[j] + b[j];
-        }
+        for (int j = 0; j < cpb; ++j) a[j] = (b[0][j] + b[1][j]) + (b[2][j] + b[3][j]);
         split_block<P, NV>(A, block_off(k, u) + hoff, u, rin[k][i], rv[k][i], a);
       }
     }
