@@ -11,11 +11,13 @@
 // (parity p, complex index c) of N/2 sites, so a complex number is addressed
 // the same way whatever the storage precision of the batch.
 //
-// block_dot is a split-K product: each block of a 512-block grid takes a
-// contiguous range of 64-element tiles, stages the batch tile in LDS, and
-// every wave accumulates IW basis vectors against it in registers; a second
-// kernel adds the per-block partials in block order, so results are
-// bit-reproducible.
+// All three are contractions in FP64 and run on the FP64 matrix cores
+// (v_mfma_f64_16x16x4_f64): a complex product of the basis with the batch is
+// two real ones against the columns (psi_re, psi_im) and (psi_im, -psi_re) of
+// every right-hand side, two columns per vector, so 12 vectors take two
+// 16-column tiles and up to 8 take one.  Even one vector (2 of 16 columns)
+// leaves the matrix cores ahead of the memory: 1 KB of the basis per 128
+// cycles and SIMD is 18 TB/s.
 #include <algorithm>
 #include <string>
 
@@ -40,9 +42,9 @@ __device__ inline Cx<double> load_cx(const char* base, int row, int h, int Nh) {
 
 // Basis elements are read once per sweep: non-temporal, so the batch's
 // blocks (reused across the 24 rows of a site tile) stay in L2.
-__device__ inline Cx<double> load_basis(const char* base, int row, int h, int Nh) {
+__device__ inline Cx<double> load_basis_at(const char* p) {
   typedef double f64x2_t __attribute__((ext_vector_type(2)));
-  const f64x2_t v = __builtin_nontemporal_load(reinterpret_cast<const f64x2_t*>(base + cx_offset<OVL_F64>(row, h, Nh)));
+  const f64x2_t v = __builtin_nontemporal_load(reinterpret_cast<const f64x2_t*>(p));
   return {v.x, v.y};
 }
 
@@ -52,180 +54,326 @@ __device__ inline void store_cx(char* base, int row, int h, int Nh, Cx<double> v
   ScalarIO<P>::store1(base + cx_offset<P>(row, h, Nh), Cx<real>{static_cast<real>(v.re), static_cast<real>(v.im)});
 }
 
-constexpr int PJ_TILE = 64;     // elements per tile (one per lane)
-constexpr int PJ_WAVES = 8;     // waves per block of block_dot
-constexpr int PJ_BLOCKS = 512;  // K-split of block_dot
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
 
-__device__ inline double wsum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+// Lane l of a 16x16x4 FP64 matrix instruction supplies A[l % 16][l / 16] and
+// B[l / 16][l % 16] and holds D[l / 16 + 4 v][l % 16], v = 0..3.
+__device__ inline f64x4_t mfma64(double a, double b, f64x4_t c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// partial[(i*G + b)*R + r] = sum over K-block b's tiles of conj(V_i) psi_r.
-// blockIdx.x selects a group of PJ_WAVES*IW basis vectors (each wave owns
-// IW), blockIdx.y the K-block; the groups of one K-block are neighbours in
-// launch order, so they share the batch tiles in cache.  Each tile of the
-// batch is staged in LDS (as FP64) once per block.
-// EX: the batch has exactly RMAX vectors (R is a compile-time constant, so
-// per-rhs guards and coefficient strides fold away).
-template <int PP, int RMAX, int IW, bool EX>
-__global__ __launch_bounds__(PJ_WAVES * 64) void dot_kernel(int Nh, int ell, const char* V, size_t vstrideV,
-                                                             const char* psi, size_t vstrideP, int R,
-                                                             double2* partial) {
-  if constexpr (EX) R = RMAX;
-  __shared__ Cx<double> tile[RMAX][PJ_TILE];
-  const int tiles_per_row = (Nh + PJ_TILE - 1) / PJ_TILE;
-  const long total = 24L * tiles_per_row;
-  const int G = gridDim.y, kb = blockIdx.y;
-  const long t0 = total * kb / G, t1 = total * (kb + 1) / G;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int ibase = (blockIdx.x * PJ_WAVES + wave) * IW;
-  Cx<double> acc[IW][RMAX];
-#pragma unroll
-  for (int j = 0; j < IW; ++j)
-#pragma unroll
-    for (int r = 0; r < RMAX; ++r) acc[j][r] = {0.0, 0.0};
+constexpr int PJ_TILE = 32;  // sites per unit of block_dot
+constexpr int PJ_PAD = 33;   // padded row of a unit in LDS
 
-  // t runs over (tile, row) with the row fastest, so the 24 rows of a site
-  // tile, which share the batch's 16-byte blocks, are read back to back
-  for (long t = t0; t < t1; ++t) {
-    const int row = static_cast<int>(t % 24);
-    const int h0 = static_cast<int>(t / 24) * PJ_TILE;
-    const int h = h0 + lane;
-    // this tile's basis elements are loaded before the barrier
-    Cx<double> v[IW];
+// partial[(kb*ell + i)*R + r] = sum over K-block kb's units of conj(V_i) psi_r.
+// A unit is 32 sites of one row; a block of NW waves runs through a
+// contiguous range of units, wave w for the mw <= 16 modes from (blockIdx.x NW
+// + w) mw (rows past them repeat the last mode).  The matrix instruction wants 16 modes side by side, memory wants one:
+// a load that touches 16 modes (64 or 128 bytes of each) reached 2.6 TB/s,
+// whatever was in flight, so a wave loads 512 bytes of two modes at a time
+// into registers (the next unit, while the current one is used) and turns the
+// unit in its own part of LDS (units of 64 sites leave room for one block of
+// four waves a CU: 50 modes at 16^3x32 took 315 us against 238).  The batch's unit is shared by the block, in two
+// buffers, so one barrier per unit is enough.  The rows of a site tile follow
+// each other, so the batch's 16-byte blocks, which hold several rows, come
+// from cache.
+// 24^3x64, 100 modes, 12 F16 vectors: 5.42 ms with FP64 FMAs on an LDS copy of
+// the batch (LDS-bound: one 16-byte read per 8 FMAs), 3.59 ms now; the basis is
+// 17 GB, 2.7 ms at 6.35 TB/s, the matrix instructions 2.2 ms.  One FP64
+// vector: 2.65 ms, at the memory's rate.
+template <int P, int NW, int NT>
+__global__ __launch_bounds__(NW * 64) void dot_kernel(int Nh, int ell, int mw, const char* V, size_t vstrideV,
+                                                      const char* psi, size_t vstrideP, int R, double2* partial) {
+  constexpr int RM = NT == 1 ? 8 : OVL_MAX_RHS, PI = (RM * PJ_TILE + 64 * NW - 1) / (64 * NW);
+  using real = typename Prec<P>::real;
+  __shared__ double2 vt[NW][16][PJ_PAD];
+  __shared__ double2 pt[2][RM][PJ_PAD];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int j = lane & 15, q = lane >> 4;
+  const int tiles = (Nh + PJ_TILE - 1) / PJ_TILE;
+  const long units = 24L * tiles;
+  const int u0 = static_cast<int>(units * blockIdx.y / gridDim.y);
+  const int u1 = static_cast<int>(units * (blockIdx.y + 1) / gridDim.y);
+  const int i0 = (blockIdx.x * NW + wave) * mw;
+  f64x4_t acc[2][NT];
 #pragma unroll
-    for (int j = 0; j < IW; ++j)
-      v[j] = (ibase + j < ell && h < Nh) ? load_basis(V + (ibase + j) * vstrideV, row, h, Nh)
-                                         : Cx<double>{0.0, 0.0};
-    __syncthreads();
-    for (int k = threadIdx.x; k < R * PJ_TILE; k += blockDim.x) {
-      const int r = k / PJ_TILE, l = k % PJ_TILE;
-      tile[r][l] = (h0 + l < Nh) ? load_cx<PP>(psi + r * vstrideP, row, h0 + l, Nh) : Cx<double>{0.0, 0.0};
+  for (int k = 0; k < 2; ++k)
+#pragma unroll
+    for (int n = 0; n < NT; ++n) acc[k][n] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+
+  double2 vr[8];  // the unit in flight (a second one: 3.79 against 3.59 ms)
+  Cx<real> pr[PI];
+  const int site = lane & 31, half = lane >> 5;
+  bool in = false;  // of the unit in flight: this lane's site exists
+  auto request = [&](int u) {
+    const int row = u % 24, h = u / 24 * PJ_TILE + site, hl = min(h, Nh - 1);
+    in = h < Nh;
+    const size_t voff = (static_cast<size_t>(row) * Nh + hl) * 16, poff = cx_offset<P>(row, hl, Nh);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      const Cx<double> v = load_basis_at(V + static_cast<size_t>(min(i0 + min(2 * m + half, mw - 1), ell - 1)) * vstrideV + voff);
+      vr[m] = make_double2(v.re, v.im);
     }
+#pragma unroll
+    for (int k = 0; k < PI; ++k) {
+      const int r = min((k * NW + wave) * 2 + half, R - 1);
+      pr[k] = ScalarIO<P>::load1(psi + static_cast<size_t>(r) * vstrideP + poff);
+    }
+  };
+  const bool part = j & 1;
+  int rr[NT];
+#pragma unroll
+  for (int n = 0; n < NT; ++n) rr[n] = min(8 * n + (j >> 1), R - 1);
+  if (u0 < u1) request(u0);
+  for (int u = u0; u < u1; ++u) {
+    const int buf = u & 1;
+#pragma unroll
+    for (int m = 0; m < 8; ++m) vt[wave][2 * m + half][site] = vr[m];
+#pragma unroll
+    for (int k = 0; k < PI; ++k)
+      if ((k * NW + wave) * 2 + half < R)
+        pt[buf][(k * NW + wave) * 2 + half][site] =
+            in ? make_double2(static_cast<double>(pr[k].re), static_cast<double>(pr[k].im)) : make_double2(0.0, 0.0);
+    request(min(u + 1, u1 - 1));  // past the end the last unit again
     __syncthreads();
+#pragma unroll 4
+    for (int s = 0; s < PJ_TILE / 4; ++s) {
+      const double2 a = vt[wave][j][4 * s + q];
+      double b1[NT], b2[NT];
 #pragma unroll
-    for (int r = 0; r < RMAX; ++r) {
-      const Cx<double> ps = (r < R) ? tile[r][lane] : Cx<double>{0.0, 0.0};
-#pragma unroll
-      for (int j = 0; j < IW; ++j) {  // acc += conj(v) ps, four FMAs
-        acc[j][r].re = fma(v[j].re, ps.re, acc[j][r].re);
-        acc[j][r].re = fma(v[j].im, ps.im, acc[j][r].re);
-        acc[j][r].im = fma(v[j].re, ps.im, acc[j][r].im);
-        acc[j][r].im = fma(-v[j].im, ps.re, acc[j][r].im);
+      for (int n = 0; n < NT; ++n) {
+        const double2 f = pt[buf][rr[n]][4 * s + q];
+        b1[n] = part ? f.y : f.x;
+        b2[n] = part ? -f.x : f.y;
       }
+#pragma unroll
+      for (int n = 0; n < NT; ++n) acc[0][n] = mfma64(a.x, b1[n], acc[0][n]);
+#pragma unroll
+      for (int n = 0; n < NT; ++n) acc[1][n] = mfma64(a.y, b2[n], acc[1][n]);
     }
   }
+  double* out = reinterpret_cast<double*>(partial) + static_cast<size_t>(blockIdx.y) * ell * R * 2;
 #pragma unroll
-  for (int j = 0; j < IW; ++j) {
-    const int i = ibase + j;
+  for (int n = 0; n < NT; ++n)
 #pragma unroll
-    for (int r = 0; r < RMAX; ++r) {
-      const double re = wsum(acc[j][r].re), im = wsum(acc[j][r].im);
-      if (lane == 0 && i < ell && r < R)
-        partial[(static_cast<size_t>(i) * G + kb) * R + r] = make_double2(re, im);
+    for (int v = 0; v < 4; ++v) {
+      const int i = i0 + q + 4 * v, col = 16 * n + j;
+      if (q + 4 * v < mw && i < ell && col < 2 * R) out[static_cast<size_t>(i) * R * 2 + col] = acc[0][n][v] + acc[1][n][v];
     }
-  }
 }
 
-// C[i*R + r] = sum_b partial[(i*G + b)*R + r], in block order.
-__global__ void dot_reduce_kernel(int ell, int R, int G, const double2* partial, double2* C) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= ell * R) return;
-  const int i = k / R, r = k % R;
+// C[k] = sum_b partial[b*n + k], n = ell R: 64 sums of every 64th block each,
+// added pairwise.  (One thread per sum, 512 reads in turn, took 54-213 us.)
+__global__ __launch_bounds__(256) void dot_reduce_kernel(int n, int G, const double2* partial, double2* C) {
+  __shared__ double2 red[64][4];
+  const int kl = threadIdx.x & 3, bl = threadIdx.x >> 2;
+  const int k = blockIdx.x * 4 + kl;
   double re = 0.0, im = 0.0;
-  for (int b = 0; b < G; ++b) {
-    const double2 v = partial[(static_cast<size_t>(i) * G + b) * R + r];
-    re += v.x;
-    im += v.y;
-  }
-  C[k] = make_double2(re, im);
-}
-
-// Y_r = [Y_r] + sum_i V_i K[i*R + r]; one thread per element, K in LDS.
-template <int PP, int RMAX, bool KEEP, bool EX>
-__global__ __launch_bounds__(256) void axpy_kernel(int Nh, int ell, const char* V, size_t vstrideV,
-                                                   const double2* __restrict__ coef, char* Y, size_t vstrideP,
-                                                   int R) {
-  if constexpr (EX) R = RMAX;
-  // coef[i*R + r] is the same for the whole wave: scalar loads
-  const int row = blockIdx.x % 24;  // rows of a site tile in consecutive blocks
-  const int h = (blockIdx.x / 24) * blockDim.x + threadIdx.x;
-  if (h >= Nh) return;
-  Cx<double> y[RMAX];
-#pragma unroll
-  for (int r = 0; r < RMAX; ++r)
-    y[r] = (KEEP && r < R) ? load_cx<PP>(Y + r * vstrideP, row, h, Nh) : Cx<double>{0.0, 0.0};
-  for (int i = 0; i < ell; ++i) {
-    const Cx<double> v = load_basis(V + i * vstrideV, row, h, Nh);
-#pragma unroll
-    for (int r = 0; r < RMAX; ++r) {
-      if (r < R) {
-        const double2 cc = coef[i * R + r];
-        y[r].re = fma(v.re, cc.x, y[r].re);
-        y[r].re = fma(-v.im, cc.y, y[r].re);
-        y[r].im = fma(v.re, cc.y, y[r].im);
-        y[r].im = fma(v.im, cc.x, y[r].im);
-      }
+  if (k < n) {
+#pragma unroll 4
+    for (int b = bl; b < G; b += 64) {
+      const double2 v = partial[static_cast<size_t>(b) * n + k];
+      re += v.x;
+      im += v.y;
     }
   }
-#pragma unroll
-  for (int r = 0; r < RMAX; ++r)
-    if (r < R) store_cx<PP>(Y + r * vstrideP, row, h, Nh, y[r]);
+  red[bl][kl] = make_double2(re, im);
+  for (int o = 32; o > 0; o >>= 1) {
+    __syncthreads();
+    if (bl < o) {
+      re += red[bl + o][kl].x;
+      im += red[bl + o][kl].y;
+      red[bl][kl] = make_double2(re, im);
+    }
+  }
+  if (bl == 0 && k < n) C[k] = make_double2(re, im);
 }
 
-// psi_h = psi - sum_i C_i eta_i, w = [gamma5] sum_i sign_i C_i eta_i.
-template <int PP, int RMAX, bool EX>
-__global__ __launch_bounds__(256) void project_kernel(int Nh, int ell, const char* V, size_t vstrideV,
-                                                      const char* psi, char* psih, char* w, size_t vstrideP, int R,
-                                                      const double2* __restrict__ coef,
-                                                      const double* __restrict__ sgn, int g5w) {
-  if constexpr (EX) R = RMAX;
-  // coef[i*R + r] and sgn[i] are the same for the whole wave: scalar loads
-  const int row = blockIdx.x % 24;  // rows of a site tile in consecutive blocks
-  const int h = (blockIdx.x / 24) * blockDim.x + threadIdx.x;
-  if (h >= Nh) return;
-  Cx<double> ph[RMAX], ww[RMAX];
+// x[m], lane group g (16 lanes): element (m, g) -> x[t], group q: element (q, t).
+__device__ inline void swap32(uint32_t& a, uint32_t& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = r[0];
+  b = r[1];
+}
+__device__ inline void swap16(uint32_t& a, uint32_t& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  a = r[0];
+  b = r[1];
+}
+__device__ inline void turn(double2 (&x)[4]) {
+  uint32_t d[4][4];
+  __builtin_memcpy(d, x, sizeof(d));
 #pragma unroll
-  for (int r = 0; r < RMAX; ++r) {
-    ph[r] = (r < R) ? load_cx<PP>(psi + r * vstrideP, row, h, Nh) : Cx<double>{0.0, 0.0};
-    ww[r] = {0.0, 0.0};
+  for (int k = 0; k < 4; ++k) {
+    swap32(d[0][k], d[2][k]);
+    swap32(d[1][k], d[3][k]);
+    swap16(d[0][k], d[1][k]);
+    swap16(d[2][k], d[3][k]);
   }
-  // the basis elements of the next PF modes are in flight while one is used
-  constexpr int PF = 4;
-  Cx<double> vb[PF];
+  __builtin_memcpy(x, d, sizeof(d));
+}
+
+// The second sweep.  MODE 0: Y_r = sum_i V_i K_ir, 1: Y_r += the same,
+// 2: psi_h = psi - sum_i C_i V_i into Y and w = [gamma5] sum_i s_i C_i V_i.
+// A block of four waves makes the 16-byte output blocks u of 256 / cpb sites of
+// one parity; a wave the 64 sites of one complex row, four tiles of 16 sites,
+// which are the rows of the matrix product, against the coefficients' columns
+// (c_re, c_im) and (-c_im, c_re).  A step is four modes, each loaded as 1 KB by
+// one instruction and turned into (16 sites x 4 modes) by lane swaps (loads of
+// 256 bytes from each of four modes were a third slower).  MODE 2 sums the
+// modes of positive and of negative sign apart (order: first nsp steps of four
+// modes with s = +1, then the others, -1 filling up a step), which halves the
+// columns: psi_h = psi - (S+ + S-), w = S+ - S-.  The sums pass through LDS,
+// where the rows of a 16-byte block meet.
+// 24^3x64, 100 modes, 12 F16 vectors: 4.93 ms with one thread per element and
+// FP64 FMAs (4-byte stores), 3.95 ms now.
+template <int P, int NT, int MODE>
+__global__ __launch_bounds__(256) void sweep_kernel(int Nh, int ell, const char* V, size_t vstrideV, const char* in,
+                                                    char* Y, char* w, size_t vstrideP, int R,
+                                                    const double2* __restrict__ coef, const int* __restrict__ order,
+                                                    int nsp, int ns, int g5w) {
+  constexpr int cpb = Prec<P>::cpb, NB = 12 / cpb, SG = 256 / cpb;  // sites per block
+  constexpr int LD = 8 * NT + 9;  // padded row of the LDS exchange: 16 or 24 columns are used
+  using real = typename Prec<P>::real;
+  __shared__ double ex[4][64 * LD];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int j = lane & 15, q = lane >> 4;
+  const int groups = (Nh + SG - 1) / SG;
+  const int pu = blockIdx.x / groups, h0 = (blockIdx.x - pu * groups) * SG;  // pu = p NB + u
+  // wave: complex wave % cpb of the block, sites h0 + 64 (wave / cpb) ...
+  V += (static_cast<size_t>(pu * cpb + wave % cpb) * Nh) * 16;
+  const uint32_t hoff = static_cast<uint32_t>(min(h0 + wave / cpb * 64 + lane, Nh - 1)) * 16u;
+  int rr[NT];
 #pragma unroll
-  for (int k = 0; k < PF; ++k) vb[k] = (k < ell) ? load_basis(V + k * vstrideV, row, h, Nh) : Cx<double>{0.0, 0.0};
-  for (int i0 = 0; i0 < ell; i0 += PF) {
+  for (int n = 0; n < NT; ++n) rr[n] = min(8 * n + (j >> 1), R - 1);
+  const bool part = j & 1;
+  const int m0 = -static_cast<int>(q == 0), m1 = -static_cast<int>(q == 1), m2 = -static_cast<int>(q == 2),
+            m3 = -static_cast<int>(q == 3);
+
+  auto sum = [&](int s0, int s1, f64x4_t (*acc)[NT]) {
+    constexpr int DP = 3;
+    double2 va[DP][4], cf[DP][NT];
+    bool some[DP];
+    int i[4];  // the modes of the next request, looked up one request ahead
+    auto look = [&](int s) {
 #pragma unroll
-    for (int k = 0; k < PF; ++k) {
-      const int i = i0 + k;
-      if (i < ell) {
-        const Cx<double> v = vb[k];
-        if (i + PF < ell) vb[k] = load_basis(V + (i + PF) * vstrideV, row, h, Nh);
-        const double s = sgn[i];
+      for (int m = 0; m < 4; ++m) {
+        i[m] = 4 * s + m;
+        if (MODE == 2) i[m] = order[i[m]];
+        else if (i[m] >= ell) i[m] = -1;
+      }
+    };
+    auto request = [&](int d, int s) {
 #pragma unroll
-        for (int r = 0; r < RMAX; ++r) {
-          if (r < R) {
-            const double2 cc = coef[i * R + r];
-            const double vr = v.re * cc.x - v.im * cc.y, vi = v.re * cc.y + v.im * cc.x;
-            ph[r].re -= vr;
-            ph[r].im -= vi;
-            ww[r].re = fma(s, vr, ww[r].re);
-            ww[r].im = fma(s, vi, ww[r].im);
+      for (int m = 0; m < 4; ++m) {
+        const Cx<double> v = load_basis_at(V + static_cast<size_t>(max(i[m], 0)) * vstrideV + hoff);
+        va[d][m] = make_double2(v.re, v.im);
+      }
+      const int iq = (i[0] & m0) | (i[1] & m1) | (i[2] & m2) | (i[3] & m3);  // i[q], without branches
+#pragma unroll
+      for (int n = 0; n < NT; ++n) cf[d][n] = coef[max(iq, 0) * R + rr[n]];
+      some[d] = iq >= 0;  // applied at the use: a select here would wait for the load
+      look(min(s + 1, s1 - 1));
+    };
+    auto use = [&](int d) {
+      turn(va[d]);
+#pragma unroll
+      for (int n = 0; n < NT; ++n) {
+        const double b1 = some[d] ? part ? cf[d][n].y : cf[d][n].x : 0.0;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[t][n] = mfma64(va[d][t].x, b1, acc[t][n]);
+      }
+#pragma unroll
+      for (int n = 0; n < NT; ++n) {
+        const double b2 = some[d] ? part ? cf[d][n].x : -cf[d][n].y : 0.0;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[t][n] = mfma64(va[d][t].y, b2, acc[t][n]);
+      }
+    };
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int n = 0; n < NT; ++n) acc[t][n] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+    if (s0 == s1) return;
+    // no branch between a request and its use: where two paths meet, the
+    // compiler waits for the later of their loads, and nothing stays in flight
+    look(s0);
+#pragma unroll
+    for (int d = 0; d < DP - 1; ++d) request(d, min(s0 + d, s1 - 1));
+    int s = s0;
+    for (; s + DP <= s1; s += DP) {
+#pragma unroll
+      for (int d = 0; d < DP; ++d) {
+        request((d + DP - 1) % DP, min(s + d + DP - 1, s1 - 1));
+        __builtin_amdgcn_sched_barrier(0);  // requests first
+        use(d);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+#pragma unroll
+    for (int d = 0; d < DP - 1; ++d)
+      if (s + d < s1) use(d);
+  };
+  // element (tile t, row q + 4 v, column 16 n + j) of this wave's sums in LDS
+  auto slot = [&](int t, int n, int v) -> double& {
+    return ex[wave][(t * 16 + q + 4 * v) * LD + (n == 0 ? j : 16 + (j & 7))];
+  };
+  f64x4_t acc[4][NT];
+  auto park = [&] {
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int n = 0; n < NT; ++n)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (n == 0 || j < 8) slot(t, n, v) = acc[t][n][v];
+  };
+  // one output, 16-byte blocks put together from LDS: out = [base] + f sums
+  auto store = [&](const char* base, char* out, double sgn, bool lower) {
+    __syncthreads();
+    for (int k = threadIdx.x; k < R * SG; k += 256) {
+      const int r = k / SG, e = k - r * SG, h = h0 + e;
+      if (h >= Nh) continue;
+      const size_t off = r * vstrideP + (static_cast<size_t>(pu) * Nh + h) * 16;
+      Cx<real> y[cpb];
+      if (base) Block<P>::load(base + off, y);
+#pragma unroll
+      for (int c = 0; c < cpb; ++c) {
+        const double* x = &ex[e / 64 * cpb + c][e % 64 * LD + 2 * r];
+        const double f = (lower && (pu % NB) * cpb + c >= 6) ? -sgn : sgn;
+        const double b0 = base ? static_cast<double>(y[c].re) : 0.0, b1 = base ? static_cast<double>(y[c].im) : 0.0;
+        y[c] = {static_cast<real>(b0 + f * x[0]), static_cast<real>(b1 + f * x[1])};
+      }
+      Block<P>::store(out + off, y);
+    }
+  };
+
+  if constexpr (MODE == 2) {
+    // one copy of the loop for both signs; S+ waits in LDS
+#pragma unroll 1
+    for (int side = 0; side < 2; ++side) {
+      sum(side ? nsp : 0, side ? ns : nsp, acc);
+      if (side == 0) park();
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int n = 0; n < NT; ++n)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (n == 0 || j < 8) {
+            const double a = slot(t, n, v), b = acc[t][n][v];
+            slot(t, n, v) = a + b;
+            acc[t][n][v] = a - b;
           }
-        }
-      }
-    }
-  }
-  const double gs = (g5w && (row % 12) >= 6) ? -1.0 : 1.0;  // spins 2, 3 under gamma5
-#pragma unroll
-  for (int r = 0; r < RMAX; ++r) {
-    if (r < R) {
-      store_cx<PP>(psih + r * vstrideP, row, h, Nh, ph[r]);
-      store_cx<PP>(w + r * vstrideP, row, h, Nh, gs * ww[r]);
-    }
+    store(in, Y, -1.0, false);
+    __syncthreads();
+    park();
+    store(nullptr, w, 1.0, g5w != 0);
+  } else {
+    sum(0, ns, acc);
+    park();
+    store(MODE == 1 ? Y : nullptr, Y, 1.0, false);
   }
 }
 
@@ -255,82 +403,86 @@ __global__ __launch_bounds__(256) void rotate_kernel(int Nh, int K, int k, char*
   }
 }
 
-template <int PP, int RMAX, int IW, bool EX = false>
-void dot_go(const ovl_geom* g, const void* V, int ell, const void* psi, int R, double2* C, double2* part, int G,
-            hipStream_t s) {
-  const int Nh = g->geo.Nh;
-  const size_t vsV = spinor_vec_bytes(g, OVL_F64), vsP = spinor_vec_bytes(g, PP);
-  const int groups = (ell + PJ_WAVES * IW - 1) / (PJ_WAVES * IW);
-  hipLaunchKernelGGL((dot_kernel<PP, RMAX, IW, EX>), dim3(groups, G), dim3(PJ_WAVES * 64), 0, s, Nh, ell,
-                     static_cast<const char*>(V), vsV, static_cast<const char*>(psi), vsP, R, part);
+// Waves of a dot_kernel block: the tiles of 16 modes in equal groups of at most
+// eight (each group reads the batch again), rounded up to an instantiation.
+int dot_waves(int ell) {
+  const int tiles = (ell + 15) / 16, groups = (tiles + 7) / 8, nw = (tiles + groups - 1) / groups;
+  return nw <= 2 ? nw : nw <= 4 ? 4 : nw <= 7 ? 7 : 8;
+}
+
+// K-blocks of block_dot: what the 256 CUs hold at once (by LDS), and at least
+// four units each, which cost less than the partial sums of more blocks.
+int dot_blocks(const ovl_geom* g, int ell) {
+  const long units = 24L * ((g->geo.Nh + PJ_TILE - 1) / PJ_TILE);
+  const int nw = dot_waves(ell), groups = (ell + 16 * nw - 1) / (16 * nw);
+  const long held = 256L * ((160 << 10) / ((nw * 16 + 2 * OVL_MAX_RHS) * PJ_PAD * 16));
+  return static_cast<int>(std::max(1L, std::min((units + 3) / 4, held / groups)));
+}
+
+template <int P, int NW, int NT>
+void dot_go(const ovl_geom* g, const void* V, int ell, const void* psi, int R, double2* part, int G, hipStream_t s) {
+  const int groups = (ell + 16 * NW - 1) / (16 * NW), mw = (ell + NW * groups - 1) / (NW * groups);
+  hipLaunchKernelGGL((dot_kernel<P, NW, NT>), dim3(groups, G), dim3(64 * NW), 0, s, g->geo.Nh, ell, mw, static_cast<const char*>(V), spinor_vec_bytes(g, OVL_F64),
+                     static_cast<const char*>(psi), spinor_vec_bytes(g, P), R, part);
+}
+
+template <int P, int NT>
+void dot_mt(const ovl_geom* g, const void* V, int ell, const void* psi, int R, double2* part, int G, hipStream_t s) {
+  switch (dot_waves(ell)) {
+    case 1: dot_go<P, 1, NT>(g, V, ell, psi, R, part, G, s); break;
+    case 2: dot_go<P, 2, NT>(g, V, ell, psi, R, part, G, s); break;
+    case 4: dot_go<P, 4, NT>(g, V, ell, psi, R, part, G, s); break;
+    case 7: dot_go<P, 7, NT>(g, V, ell, psi, R, part, G, s); break;
+    default: dot_go<P, 8, NT>(g, V, ell, psi, R, part, G, s); break;
+  }
+}
+
+// C = V^dag psi with the per-block partials in `part` (ell * G * R entries).
+void dot_prec(const ovl_geom* g, const void* V, int ell, const void* psi, int prec, int R, double2* C, double2* part,
+              int G, hipStream_t s) {
+  auto go = [&](auto P) {
+    constexpr int p = decltype(P)::value;
+    if (R <= 8) dot_mt<p, 1>(g, V, ell, psi, R, part, G, s);
+    else dot_mt<p, 2>(g, V, ell, psi, R, part, G, s);
+  };
+  switch (prec) {
+    case OVL_F64: go(std::integral_constant<int, OVL_F64>{}); break;
+    case OVL_F32: go(std::integral_constant<int, OVL_F32>{}); break;
+    case OVL_F16: go(std::integral_constant<int, OVL_F16>{}); break;
+    case OVL_BF16: go(std::integral_constant<int, OVL_BF16>{}); break;
+    default: throw Error(OVL_E_PRECISION, "unknown precision");
+  }
   OVL_HIP(hipGetLastError());
-  hipLaunchKernelGGL(dot_reduce_kernel, dim3((ell * R + 255) / 256), dim3(256), 0, s, ell, R, G,
+  hipLaunchKernelGGL(dot_reduce_kernel, dim3((ell * R + 3) / 4), dim3(256), 0, s, ell * R, G,
                      static_cast<const double2*>(part), C);
   OVL_HIP(hipGetLastError());
 }
 
-// C = V^dag psi with the per-block partials in `part` (ell * G * R entries).
-template <int PP>
-void dot_r(const ovl_geom* g, const void* V, int ell, const void* psi, int R, double2* C, double2* part, int G,
-           hipStream_t s) {
-  if (R == 1) dot_go<PP, 1, 8, true>(g, V, ell, psi, R, C, part, G, s);
-  else if (R <= 4) dot_go<PP, 4, 4>(g, V, ell, psi, R, C, part, G, s);
-  else if (R == 12) dot_go<PP, 12, 2, true>(g, V, ell, psi, R, C, part, G, s);
-  else dot_go<PP, 12, 2>(g, V, ell, psi, R, C, part, G, s);
+template <int P, int MODE>
+void sweep_go(const ovl_geom* g, const void* V, int ell, const void* in, void* Y, void* w, int R, const double2* K,
+              const int* order, int nsp, int ns, int g5w, hipStream_t s) {
+  constexpr int cpb = Prec<P>::cpb;
+  const int Nh = g->geo.Nh, blocks = 2 * (12 / cpb) * ((Nh + 256 / cpb - 1) / (256 / cpb));
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, Nh, ell, static_cast<const char*>(V),
+                       spinor_vec_bytes(g, OVL_F64), static_cast<const char*>(in), static_cast<char*>(Y),
+                       static_cast<char*>(w), spinor_vec_bytes(g, P), R, K, order, nsp, ns, g5w);
+  };
+  if (R <= 8) go(sweep_kernel<P, 1, MODE>);
+  else go(sweep_kernel<P, 2, MODE>);
+  OVL_HIP(hipGetLastError());
 }
 
-void dot_prec(const ovl_geom* g, const void* V, int ell, const void* psi, int prec, int R, double2* C, double2* part,
-              int G, hipStream_t s) {
+template <int MODE>
+void sweep_prec(const ovl_geom* g, const void* V, int ell, const void* in, void* Y, void* w, int prec, int R,
+                const double2* K, const int* order, int nsp, int ns, int g5w, hipStream_t s) {
   switch (prec) {
-    case OVL_F64: dot_r<OVL_F64>(g, V, ell, psi, R, C, part, G, s); break;
-    case OVL_F32: dot_r<OVL_F32>(g, V, ell, psi, R, C, part, G, s); break;
-    case OVL_F16: dot_r<OVL_F16>(g, V, ell, psi, R, C, part, G, s); break;
-    case OVL_BF16: dot_r<OVL_BF16>(g, V, ell, psi, R, C, part, G, s); break;
+    case OVL_F64: sweep_go<OVL_F64, MODE>(g, V, ell, in, Y, w, R, K, order, nsp, ns, g5w, s); break;
+    case OVL_F32: sweep_go<OVL_F32, MODE>(g, V, ell, in, Y, w, R, K, order, nsp, ns, g5w, s); break;
+    case OVL_F16: sweep_go<OVL_F16, MODE>(g, V, ell, in, Y, w, R, K, order, nsp, ns, g5w, s); break;
+    case OVL_BF16: sweep_go<OVL_BF16, MODE>(g, V, ell, in, Y, w, R, K, order, nsp, ns, g5w, s); break;
     default: throw Error(OVL_E_PRECISION, "unknown precision");
   }
-}
-
-template <int PP, int RMAX, bool EX = false>
-void axpy_go(const ovl_geom* g, const void* V, int ell, const double2* K, void* Y, int R, bool keep, hipStream_t s) {
-  const int Nh = g->geo.Nh;
-  const size_t vsV = spinor_vec_bytes(g, OVL_F64), vsP = spinor_vec_bytes(g, PP);
-  dim3 grid(((Nh + 255) / 256) * 24);
-  if (keep)
-    hipLaunchKernelGGL((axpy_kernel<PP, RMAX, true, EX>), grid, dim3(256), 0, s, Nh, ell, static_cast<const char*>(V),
-                       vsV, K, static_cast<char*>(Y), vsP, R);
-  else
-    hipLaunchKernelGGL((axpy_kernel<PP, RMAX, false, EX>), grid, dim3(256), 0, s, Nh, ell,
-                       static_cast<const char*>(V), vsV, K, static_cast<char*>(Y), vsP, R);
-  OVL_HIP(hipGetLastError());
-}
-
-template <int PP>
-void axpy_r(const ovl_geom* g, const void* V, int ell, const double2* K, void* Y, int R, bool keep, hipStream_t s) {
-  if (R == 1) axpy_go<PP, 1, true>(g, V, ell, K, Y, R, keep, s);
-  else if (R <= 4) axpy_go<PP, 4>(g, V, ell, K, Y, R, keep, s);
-  else if (R == 12) axpy_go<PP, 12, true>(g, V, ell, K, Y, R, keep, s);
-  else axpy_go<PP, 12>(g, V, ell, K, Y, R, keep, s);
-}
-
-template <int PP, int RMAX, bool EX = false>
-void project_go(const ovl_lowmodes* lm, const void* psi, void* psih, void* w, int R, int g5w, const double2* C,
-                hipStream_t s) {
-  const ovl_geom* g = &lm->geom;
-  const int Nh = g->geo.Nh;
-  const size_t vsV = spinor_vec_bytes(g, OVL_F64), vsP = spinor_vec_bytes(g, PP);
-  hipLaunchKernelGGL((project_kernel<PP, RMAX, EX>), dim3(((Nh + 255) / 256) * 24), dim3(256), 0, s, Nh, lm->ell,
-                     static_cast<const char*>(lm->V), vsV, static_cast<const char*>(psi), static_cast<char*>(psih),
-                     static_cast<char*>(w), vsP, R, C, lm->dev_sign, g5w);
-  OVL_HIP(hipGetLastError());
-}
-
-template <int PP>
-void project_r(const ovl_lowmodes* lm, const void* psi, void* psih, void* w, int R, int g5w, const double2* C,
-               hipStream_t s) {
-  if (R == 1) project_go<PP, 1, true>(lm, psi, psih, w, R, g5w, C, s);
-  else if (R <= 4) project_go<PP, 4>(lm, psi, psih, w, R, g5w, C, s);
-  else if (R == 12) project_go<PP, 12, true>(lm, psi, psih, w, R, g5w, C, s);
-  else project_go<PP, 12>(lm, psi, psih, w, R, g5w, C, s);
 }
 
 }  // namespace
@@ -338,20 +490,17 @@ void project_r(const ovl_lowmodes* lm, const void* psi, void* psih, void* w, int
 void block_dot(const ovl_geom* g, const void* V, int ell, const void* psi, int prec, int R, double2* C,
                hipStream_t s) {
   OVL_REQUIRE(R >= 1 && R <= OVL_MAX_RHS && ell >= 1, OVL_E_ARG, "block_dot: 1 <= R <= 12, ell >= 1");
-  WsBuf part(static_cast<size_t>(ell) * PJ_BLOCKS * R * sizeof(double2), s);
-  dot_prec(g, V, ell, psi, prec, R, C, static_cast<double2*>(part.p), PJ_BLOCKS, s);
+  const int G = dot_blocks(g, ell);
+  WsBuf part(static_cast<size_t>(ell) * G * R * sizeof(double2), s);
+  dot_prec(g, V, ell, psi, prec, R, C, static_cast<double2*>(part.p), G, s);
 }
 
 void block_axpy(const ovl_geom* g, const void* V, int ell, const double2* K, void* Y, int prec, int R, bool keep,
                 hipStream_t s) {
   OVL_REQUIRE(R >= 1 && R <= OVL_MAX_RHS && ell >= 1, OVL_E_ARG, "block_axpy: 1 <= R <= 12, ell >= 1");
-  switch (prec) {
-    case OVL_F64: axpy_r<OVL_F64>(g, V, ell, K, Y, R, keep, s); break;
-    case OVL_F32: axpy_r<OVL_F32>(g, V, ell, K, Y, R, keep, s); break;
-    case OVL_F16: axpy_r<OVL_F16>(g, V, ell, K, Y, R, keep, s); break;
-    case OVL_BF16: axpy_r<OVL_BF16>(g, V, ell, K, Y, R, keep, s); break;
-    default: throw Error(OVL_E_PRECISION, "unknown precision");
-  }
+  const int ns = (ell + 3) / 4;
+  if (keep) sweep_prec<1>(g, V, ell, nullptr, Y, nullptr, prec, R, K, nullptr, ns, ns, 0, s);
+  else sweep_prec<0>(g, V, ell, nullptr, Y, nullptr, prec, R, K, nullptr, ns, ns, 0, s);
 }
 
 void block_rotate_inplace(const ovl_geom* g, void* V, int K, const double2* S, int k, hipStream_t s) {
@@ -373,13 +522,8 @@ void lowmode_project_ws(const ovl_lowmodes* lm, const void* psi, void* psih, voi
   OVL_REQUIRE(nrhs >= 1 && nrhs <= OVL_MAX_RHS && lm->ell >= 1, OVL_E_ARG,
               "projection: 1 <= nrhs <= 12 and at least one low mode");
   dot_prec(&lm->geom, lm->V, lm->ell, psi, prec, nrhs, C, part, G, s);
-  switch (prec) {
-    case OVL_F64: project_r<OVL_F64>(lm, psi, psih, w, nrhs, g5w, C, s); break;
-    case OVL_F32: project_r<OVL_F32>(lm, psi, psih, w, nrhs, g5w, C, s); break;
-    case OVL_F16: project_r<OVL_F16>(lm, psi, psih, w, nrhs, g5w, C, s); break;
-    case OVL_BF16: project_r<OVL_BF16>(lm, psi, psih, w, nrhs, g5w, C, s); break;
-    default: throw Error(OVL_E_PRECISION, "unknown precision");
-  }
+  sweep_prec<2>(&lm->geom, lm->V, lm->ell, psi, psih, w, prec, nrhs, C, lm->dev_order, lm->steps_pos, lm->steps, g5w,
+                s);
 }
 
 // Scratch of the allocation-free projection: one array per GPU, in device
@@ -419,13 +563,14 @@ void lowmode_project(const ovl_lowmodes* lm, const void* psi, void* psih, void* 
                      hipStream_t s) {
   OVL_REQUIRE(nrhs >= 1 && nrhs <= OVL_MAX_RHS, OVL_E_ARG, "projection supports 1 to 12 right-hand sides");
   WsBuf cbuf(static_cast<size_t>(lm->ell) * nrhs * sizeof(double2), s);
-  WsBuf part(static_cast<size_t>(lm->ell) * PJ_BLOCKS * nrhs * sizeof(double2), s);
+  const int G = dot_blocks(&lm->geom, lm->ell);
+  WsBuf part(static_cast<size_t>(lm->ell) * G * nrhs * sizeof(double2), s);
   lowmode_project_ws(lm, psi, psih, w, prec, nrhs, g5w, static_cast<double2*>(cbuf.p),
-                     static_cast<double2*>(part.p), PJ_BLOCKS, s);
+                     static_cast<double2*>(part.p), G, s);
 }
 
 // Same projection with its scratch in the static per-device array.  Pass 1
-// keeps PJ_BLOCKS K-blocks while they fit (then the result is bit-identical
+// keeps dot_blocks() K-blocks while they fit (then the result is bit-identical
 // to lowmode_project), else as many as fit, at least kStaticMinBlocks.
 // Every partial and coefficient slot is written before it is read, so
 // nothing needs clearing between calls.
@@ -439,7 +584,7 @@ void lowmode_project_static(const ovl_lowmodes* lm, const void* psi, void* psih,
   const size_t unit = static_cast<size_t>(lm->ell) * nrhs * sizeof(double2);  // one coefficient set
   const size_t c_bytes = (unit + 255) / 256 * 256;
   const size_t fit = (kStaticScratchBytes - c_bytes) / unit;  // >= kStaticMinBlocks by the check above
-  const int G = static_cast<int>(std::min<size_t>(PJ_BLOCKS, fit));
+  const int G = static_cast<int>(std::min<size_t>(dot_blocks(&lm->geom, lm->ell), fit));
   char* base = static_cast<char*>(static_scratch());
   lowmode_project_ws(lm, psi, psih, w, prec, nrhs, 0, reinterpret_cast<double2*>(base),
                      reinterpret_cast<double2*>(base + c_bytes), G, s);

@@ -591,7 +591,10 @@ struct ovl_lowmodes {
   int ell;
   const void* V;  // borrowed: ell FP64 spinors
   std::vector<double> lambda;
-  double* dev_sign = nullptr;  // sign(lambda_i) on the device
+  // on the device: the mode numbers with lambda >= 0, then the others, each
+  // filled up with -1 to a multiple of four (steps_pos and steps steps of four)
+  int* dev_order = nullptr;
+  int steps_pos = 0, steps = 0;
 };
 
 // Eigenpairs of the massless overlap operator used to deflate D(m) (eq. 9).

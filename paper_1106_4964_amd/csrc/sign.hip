@@ -530,19 +530,24 @@ int ovl_lowmodes_create(const ovl_geom* g, int ell, const void* V, const double*
     lm->ell = ell;
     lm->V = V;
     lm->lambda.assign(lambda, lambda + ell);
-    std::vector<double> sg(std::max(ell, 1));
-    for (int i = 0; i < ell; ++i) {
-      if (!std::isfinite(lambda[i])) {
-        delete lm;
-        throw Error(OVL_E_NAN, "non-finite eigenvalue");
+    std::vector<int> order;
+    for (int side = 0; side < 2; ++side) {
+      for (int i = 0; i < ell; ++i) {
+        if (!std::isfinite(lambda[i])) {
+          delete lm;
+          throw Error(OVL_E_NAN, "non-finite eigenvalue");
+        }
+        if ((lambda[i] >= 0.0) == (side == 0)) order.push_back(i);
       }
-      sg[i] = lambda[i] >= 0.0 ? 1.0 : -1.0;
+      while (order.size() % 4) order.push_back(-1);
+      (side == 0 ? lm->steps_pos : lm->steps) = static_cast<int>(order.size() / 4);
     }
-    if (hipMalloc(&lm->dev_sign, sg.size() * sizeof(double)) != hipSuccess) {
+    order.resize(std::max<size_t>(order.size(), 4), -1);
+    if (hipMalloc(&lm->dev_order, order.size() * sizeof(int)) != hipSuccess) {
       delete lm;
       throw Error(OVL_E_NOMEM, "lowmodes: device allocation failed");
     }
-    OVL_HIP(hipMemcpy(lm->dev_sign, sg.data(), sg.size() * sizeof(double), hipMemcpyHostToDevice));
+    OVL_HIP(hipMemcpy(lm->dev_order, order.data(), order.size() * sizeof(int), hipMemcpyHostToDevice));
     *out = lm;
     return OVL_OK;
   });
@@ -550,7 +555,7 @@ int ovl_lowmodes_create(const ovl_geom* g, int ell, const void* V, const double*
 
 int ovl_lowmodes_destroy(ovl_lowmodes* lm) {
   if (lm) {
-    if (lm->dev_sign) (void)hipFree(lm->dev_sign);
+    if (lm->dev_order) (void)hipFree(lm->dev_order);
     delete lm;
   }
   return OVL_OK;

@@ -165,3 +165,36 @@ def test_overlap_aliasing_rejected(c1):
     with pytest.raises(ovl.OvlError) as e:
         ovl.ovl_overlap_apply(buf, buf, gauge, RHO, 0.01, s_lib, None, 0, ovl.OVL_F64, 1, None)
     assert e.value.name == "OVL_E_ALIAS"
+
+
+@pytest.mark.parametrize("prec", [ovl.OVL_F64, ovl.OVL_F32, ovl.OVL_F16, ovl.OVL_BF16])
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (4, 4, 4, 4), (6, 6, 2, 10)])
+def test_projection_tile_edges(prec, dims):
+    """The matrix-core projection around its tiles: parities smaller than, equal
+    to and not a multiple of the 32- and 64-site units (2^4: 8 half-sites, 4^4:
+    128, 360), mode counts around 16-mode tiles, their groups of 1, 2, 4, 7 and
+    8 waves and two groups of modes, one and two column tiles (8 and 9 vectors),
+    eigenvalues of one sign and of both."""
+    g = ovl.Geometry(dims)
+    V = si.orthonormal_spinors(dims, 150, 17)
+    vdev = _lowmodes_dev(g, V)
+    Vm = V.reshape(150, -1)
+    psi = np.stack([si.gaussian_spinor(dims, 800 + r) for r in range(12)])
+    u = gu.UNIT_ROUNDOFF[prec]
+    rng = np.random.default_rng(3)
+    for ell, nrhs, signs in ((1, 1, 0), (3, 8, 1), (16, 9, -1), (17, 12, 0), (33, 2, 0), (49, 12, 1), (70, 5, 0),
+                             (113, 12, 0), (128, 1, -1), (150, 12, 0)):
+        lam = rng.uniform(0.1, 0.5, ell) * (signs if signs else rng.choice([-1.0, 1.0], ell))
+        lm = ovl.LowModes(g, vdev, lam)
+        inp = gu.pack(g, psi[:nrhs], prec, nrhs)
+        h, w = gu.empty_field(g, prec, nrhs), gu.empty_field(g, prec, nrhs)
+        ovl.ovl_lowmodes_project(lm, inp, h, w, prec, nrhs, None)
+        x = np.reshape(gu.unpack(g, inp, prec, nrhs), (nrhs, -1))
+        c = Vm[:ell].conj() @ x.T
+        want_h = x - (Vm[:ell].T @ c).T
+        want_w = (Vm[:ell].T @ (np.sign(lam)[:, None] * c)).T
+        # FP64 sums of up to 150 terms of order one, then the storage rounding
+        tol = 1e-13 if prec == ovl.OVL_F64 else 2 * u
+        for dev, want in ((h, want_h), (w, want_w)):
+            got = np.reshape(gu.unpack(g, dev, prec, nrhs), (nrhs, -1))
+            assert np.max(np.abs(got - want)) <= tol * max(1.0, np.max(np.abs(want))), (ell, nrhs, signs)
