@@ -190,16 +190,6 @@ __global__ __launch_bounds__(256) void dot_reduce_kernel(int n, int G, const dou
 }
 
 // x[m], lane group g (16 lanes): element (m, g) -> x[t], group q: element (q, t).
-__device__ inline void swap32(uint32_t& a, uint32_t& b) {
-  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-  a = r[0];
-  b = r[1];
-}
-__device__ inline void swap16(uint32_t& a, uint32_t& b) {
-  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
-  a = r[0];
-  b = r[1];
-}
 __device__ inline void turn(double2 (&x)[4]) {
   uint32_t d[4][4];
   __builtin_memcpy(d, x, sizeof(d));

@@ -563,6 +563,18 @@ __device__ inline int xcd_remap(int b, int nblocks) {
   return x * q + (x < r ? x : r) + j;
 }
 
+// Lane swaps: lanes 32..63 of a with lanes 0..31 of b; the odd rows of 16
+// lanes of a with the even rows of b.
+__device__ inline void swap32(uint32_t& a, uint32_t& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = r[0];
+  b = r[1];
+}
+__device__ inline void swap16(uint32_t& a, uint32_t& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  a = r[0];
+  b = r[1];
+}
 // ------------------------------------------------------------- handles
 }  // namespace ovl
 

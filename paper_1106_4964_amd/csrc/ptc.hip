@@ -17,6 +17,7 @@
 //
 // Activations are FP32 spinors in the library layout, one vector per
 // channel; the links come from the FP32 representation of the gauge field.
+#include <algorithm>
 #include <cmath>
 #include <complex>
 
@@ -28,167 +29,309 @@ namespace {
 constexpr int NPATH = 9;
 constexpr int CMAX = 4;
 
-// T_k psi at site (p, h) for a FP32 spinor field (k in 0..8).
-template <int R>
-__device__ inline void transport(const Geo& g, const void* links, const char* f, int p, int h, const int* nb, int k,
-                                 Cx<float>* out) {
-  if (k == 0) {
-    SpinorIO<OVL_F32>::load(f, p, h, g.Nh, out);
+// Neighbours of site h in direction mu (the same for the whole wave), parity
+// 1 - p; computed where they are needed, since a run-time index into a table of
+// eight would put the table in scratch memory.
+__device__ inline void neighbors_of(const Geo& g, int h, int x, int y, int z, int t, int mu, int& fwd, int& bwd) {
+  if (mu == 0) {
+    const int base = h - (x >> 1);
+    fwd = base + ((x + 1 == g.Lx ? 0 : x + 1) >> 1);
+    bwd = base + ((x == 0 ? g.Lx - 1 : x - 1) >> 1);
     return;
   }
-  const int q = 1 - p;
-  Cx<float> s[12], u[3][3];
-  if (k <= 4) {
-    const int mu = k - 1;
-    SpinorIO<OVL_F32>::load(f, q, nb[mu], g.Nh, s);
-    LinkIO<OVL_F32, R>::load(links, mu, p, h, g.Nh, u);
+  const int c = mu == 1 ? y : mu == 2 ? z : t, L = mu == 1 ? g.Ly : mu == 2 ? g.Lz : g.Lt;
+  const int st = mu == 1 ? g.sy : mu == 2 ? g.sz : g.st;
+  fwd = h + (c + 1 == L ? -(L - 1) * st : st);
+  bwd = h + (c == 0 ? (L - 1) * st : -st);
+}
+
+// a += u v, four FMAs
+__device__ inline void cfma(Cx<float>& a, Cx<float> u, Cx<float> v) {
+  a.re = ffma(u.re, v.re, a.re);
+  a.re = ffma(-u.im, v.im, a.re);
+  a.im = ffma(u.re, v.im, a.im);
+  a.im = ffma(u.im, v.re, a.im);
+}
+
+// out += U s (DAG: U^dag s) on the colour index of the four spins, each row's
+// product summed before it is added (the sums over paths and channels then
+// round once per term; adding every product at once cost a third in accuracy).
+template <bool DAG>
+__device__ inline void colour_add(const Cx<float> (*u)[3], const Cx<float>* s, Cx<float>* out) {
 #pragma unroll
-    for (int sp = 0; sp < 4; ++sp)
+  for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        Cx<float> r = {0.f, 0.f};
+    for (int a = 0; a < 3; ++a) {
+      Cx<float> r = {0.f, 0.f};
 #pragma unroll
-        for (int b = 0; b < 3; ++b) r = r + u[a][b] * s[3 * sp + b];
-        out[3 * sp + a] = r;
+      for (int b = 0; b < 3; ++b) cfma(r, DAG ? conj(u[b][a]) : u[a][b], s[3 * sp + b]);
+      out[3 * sp + a] = out[3 * sp + a] + r;
+    }
+}
+
+// u s (CONJ: conj(u) s) with every rounding spelled out: one product of each
+// part is rounded, the other one fused; SWAP: the other way round in the
+// commutative part (im; re with CONJ).
+template <bool CONJ, bool SWAP>
+__device__ inline Cx<float> rounded_mul(Cx<float> u, Cx<float> s) {
+  const float ui = CONJ ? -u.im : u.im;
+  Cx<float> z;
+  if constexpr (CONJ && SWAP) z.re = ffma(-ui, s.im, __fmul_rn(u.re, s.re));
+  else z.re = ffma(u.re, s.re, -__fmul_rn(ui, s.im));
+  if constexpr (!CONJ && SWAP) z.im = ffma(ui, s.re, __fmul_rn(u.re, s.im));
+  else z.im = ffma(u.re, s.im, __fmul_rn(ui, s.re));
+  return z;
+}
+
+// out = U s (DAG: U^dag s) for the weight gradient, whose FP32 sums are handed
+// out in FP64: each complex product is rounded before it is added, and the
+// order within the products is the one that the first version of the kernel
+// compiled to (it differs in columns 0 and 2 of a rebuilt third row), so the
+// gradients are the same to the last bit and training runs repeat.
+template <int R, bool DAG>
+__device__ inline void colour_mul12(const Cx<float> (*u)[3], const Cx<float>* s, Cx<float>* out) {
+#pragma unroll
+  for (int sp = 0; sp < 4; ++sp)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      Cx<float> r = {0.f, 0.f};
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        const Cx<float> x = s[3 * sp + b];
+        const bool swap = R == 12 && (DAG ? b == 2 && a != 1 : a == 2 && b != 1);
+        if constexpr (DAG) r = r + (swap ? rounded_mul<true, true>(u[b][a], x) : rounded_mul<true, false>(u[b][a], x));
+        else r = r + (swap ? rounded_mul<false, true>(u[a][b], x) : rounded_mul<false, false>(u[a][b], x));
       }
-  } else {
-    const int mu = k - 5;
-    SpinorIO<OVL_F32>::load(f, q, nb[mu + 4], g.Nh, s);
-    LinkIO<OVL_F32, R>::load(links, mu, q, nb[mu + 4], g.Nh, u);
+      out[3 * sp + a] = r;
+    }
+}
+
+// out += w s, the 4x4 matrix w (16 complex numbers, the same for the whole
+// wave: scalar loads) on the spin index.
+__device__ inline void spin_add(const float2* __restrict__ w, const Cx<float>* s, Cx<float>* out) {
 #pragma unroll
-    for (int sp = 0; sp < 4; ++sp)
+  for (int r = 0; r < 4; ++r) {
+    Cx<float> z[3] = {{0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}};
 #pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        Cx<float> r = {0.f, 0.f};
+    for (int t = 0; t < 4; ++t) {
+      const float2 ww = w[4 * r + t];
 #pragma unroll
-        for (int b = 0; b < 3; ++b) r = r + cmul_conj(u[b][a], s[3 * sp + b]);
-        out[3 * sp + a] = r;
-      }
+      for (int c = 0; c < 3; ++c) cfma(z[c], Cx<float>{ww.x, ww.y}, s[3 * t + c]);
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) out[3 * r + c] = out[3 * r + c] + z[c];
   }
 }
 
-// out[a] = sum_b sum_k W[k][a][b] T_k in[b]; W in LDS as float2 [k][a][b][s][t].
+__device__ inline void clear12(Cx<float>* v) {
+#pragma unroll
+  for (int c = 0; c < 12; ++c) v[c] = {0.f, 0.f};
+}
+
+// out[a] = sum_b sum_k W[k][a][b] T_k in[b]; W as float2 [k][a][b][s][t].
 // blockIdx.y selects one field of a batch: its channels start rstride_in
-// (rstride_out) bytes after the previous field's.
-template <int R>
+// (rstride_out) bytes after the previous field's.  Colour and spin matrices
+// commute, so the transport acts where there are fewer channels: on the
+// inputs, or on the spin-mixed sums.  The channel counts are compile-time, so
+// that the accumulators are registers, and W comes through scalar loads:
+// with run-time counts and W in LDS 4 -> 1 channels took 135 us at 16^3x32,
+// now 72 (1.1 GFMA, 21 us at 51 TFMA/s; two waves per SIMD that wait for each
+// direction's loads in turn).
+template <int R, int CIN, int COUT>
 __global__ __launch_bounds__(256) void ptc_forward_kernel(Geo g, const void* links, const char* in, char* out,
-                                                          size_t vstride, int cin, int cout, const float2* W,
+                                                          size_t vstride, const float2* __restrict__ W,
                                                           size_t rstride_in, size_t rstride_out) {
-  __shared__ float2 w[NPATH * CMAX * CMAX * 16];
   in += blockIdx.y * rstride_in;
   out += blockIdx.y * rstride_out;
-  const int nw = NPATH * cin * cout * 16;
-  for (int i = threadIdx.x; i < nw; i += blockDim.x) w[i] = W[i];
-  __syncthreads();
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= 2 * g.Nh) return;
   const int p = e >= g.Nh, h = e - p * g.Nh;
-  int x, y, z, t, nb[8];
+  int x, y, z, t;
   site_coords(g, p, h, x, y, z, t);
-  site_neighbors(g, h, x, y, z, t, nb);
-  Cx<float> acc[CMAX][12];
+  Cx<float> acc[COUT][12];
 #pragma unroll
-  for (int a = 0; a < CMAX; ++a)
+  for (int a = 0; a < COUT; ++a) clear12(acc[a]);
+  auto path = [&](auto dir, int k, int q, int hn, const Cx<float> (*u)[3]) {  // dir: 0 identity, 1 U, 2 U^dag
+    constexpr int D = decltype(dir)::value;
+    const float2* w = W + static_cast<size_t>(k) * COUT * CIN * 16;
+    if constexpr (D == 0 || CIN <= COUT) {
 #pragma unroll
-    for (int c = 0; c < 12; ++c) acc[a][c] = {0.f, 0.f};
-  for (int b = 0; b < cin; ++b) {
-    for (int k = 0; k < NPATH; ++k) {
-      Cx<float> v[12];
-      transport<R>(g, links, in + b * vstride, p, h, nb, k, v);
+      for (int b = 0; b < CIN; ++b) {
+        Cx<float> s[12], v[12];
+        SpinorIO<OVL_F32>::load(in + b * vstride, q, hn, g.Nh, s);
+        if constexpr (D != 0) {
+          clear12(v);
+          colour_add<D == 2>(u, s, v);
+        }
 #pragma unroll
-      for (int a = 0; a < CMAX; ++a) {
-        if (a < cout) {
-          const float2* wk = w + ((k * cout + a) * cin + b) * 16;
+        for (int a = 0; a < COUT; ++a) spin_add(w + (a * CIN + b) * 16, D == 0 ? s : v, acc[a]);
+      }
+    } else {
+      Cx<float> v[COUT][12];
 #pragma unroll
-          for (int s = 0; s < 4; ++s)
+      for (int a = 0; a < COUT; ++a) clear12(v[a]);
 #pragma unroll
-            for (int tt = 0; tt < 4; ++tt) {
-              const float2 ww = wk[4 * s + tt];
-              const Cx<float> wc = {ww.x, ww.y};
+      for (int b = 0; b < CIN; ++b) {
+        Cx<float> s[12];
+        SpinorIO<OVL_F32>::load(in + b * vstride, q, hn, g.Nh, s);
 #pragma unroll
-              for (int c = 0; c < 3; ++c) acc[a][3 * s + c] = acc[a][3 * s + c] + wc * v[3 * tt + c];
-            }
+        for (int a = 0; a < COUT; ++a) spin_add(w + (a * CIN + b) * 16, s, v[a]);
+      }
+#pragma unroll
+      for (int a = 0; a < COUT; ++a) colour_add<D == 2>(u, v[a], acc[a]);
+    }
+  };
+  path(std::integral_constant<int, 0>{}, 0, p, h, nullptr);
+#pragma unroll 1
+  for (int mu = 0; mu < 4; ++mu) {
+    int hf, hb;
+    neighbors_of(g, h, x, y, z, t, mu, hf, hb);
+    Cx<float> u[3][3];
+    LinkIO<OVL_F32, R>::load(links, mu, p, h, g.Nh, u);
+    path(std::integral_constant<int, 1>{}, mu + 1, 1 - p, hf, u);
+    LinkIO<OVL_F32, R>::load(links, mu, 1 - p, hb, g.Nh, u);
+    path(std::integral_constant<int, 2>{}, mu + 5, 1 - p, hb, u);
+  }
+#pragma unroll
+  for (int a = 0; a < COUT; ++a) SpinorIO<OVL_F32>::store(out + a * vstride, p, h, g.Nh, acc[a]);
+}
+
+// Sums v[0..N) over the wave, the values dealt out over the lanes: every step
+// halves the lanes that share a value and the values a lane keeps, N + N/2 +
+// ... exchanges instead of 6 N, with the pairs of a butterfly (so its sums, to
+// the last bit).  On return v[0..n) are the sums of the values
+// base + 0..n; returns n (compile-time) and sets base.
+template <int N, int O>
+__device__ inline void wave_deal(float* v, int lane, int& base) {
+  if constexpr (O >= 1) {
+    if constexpr (N % 2 == 0) {
+      constexpr int H = N / 2;
+      const bool up = lane & O;
+#pragma unroll
+      for (int i = 0; i < H; ++i) {
+        if constexpr (O >= 16) {
+          uint32_t a = __builtin_bit_cast(uint32_t, v[i]), b = __builtin_bit_cast(uint32_t, v[i + H]);
+          if constexpr (O == 32) swap32(a, b);
+          else swap16(a, b);
+          v[i] = __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
+        } else {
+          const float keep = up ? v[i + H] : v[i], send = up ? v[i] : v[i + H];
+          v[i] = keep + __shfl_xor(send, O, 64);
         }
       }
+      base += up ? H : 0;
+      wave_deal<H, O / 2>(v, lane, base);
+    } else {
+#pragma unroll
+      for (int i = 0; i < N; ++i) v[i] += __shfl_xor(v[i], O, 64);
+      wave_deal<N, O / 2>(v, lane, base);
     }
   }
-  for (int a = 0; a < cout; ++a) SpinorIO<OVL_F32>::store(out + a * vstride, p, h, g.Nh, acc[a]);
+}
+constexpr int dealt(int n) {  // values a lane keeps
+  for (int o = 0; o < 6 && n % 2 == 0; ++o) n /= 2;
+  return n;
 }
 
 // partial[(k*G + block)*cout*cin*16 + ...] = sum over the block's sites of
-// g_out[a][s][c] conj(T_k in[b][t][c]).  blockIdx.y = k.
-template <int R>
+// g_out[a][s][c] conj(T_k in[b][t][c]).  blockIdx.y = k.  The channel counts
+// are compile-time (with run-time counts the 64 accumulators lived in scratch
+// memory: 376 us for 1 -> 4 channels at 16^3x32, now 71; 0.9 GFMA are 18 us).
+template <int R, int CIN, int COUT>
 __global__ __launch_bounds__(256) void ptc_wgrad_kernel(Geo g, const void* links, const char* in, const char* gout,
-                                                        size_t vstride, int cin, int cout, double2* partial) {
-  __shared__ float2 red[256 / 64][CMAX * 16];
-  const int k = blockIdx.y;
-  const int nout = cin * cout * 16;
-  Cx<float> acc[CMAX * 16];  // [a*cin+b][s][t] with cin*cout <= 4
+                                                        size_t vstride, double2* partial) {
+  constexpr int NC = CIN * COUT * 16;
+  __shared__ float2 red[256 / 64][NC];
+  const int k = blockIdx.y, mu = (k - 1) & 3;
+  union {
+    Cx<float> c[NC];  // [a*cin+b][s][t]
+    float f[2 * NC];
+  } acc;
 #pragma unroll
-  for (int i = 0; i < CMAX * 16; ++i) acc[i] = {0.f, 0.f};
+  for (int i = 0; i < NC; ++i) acc.c[i] = {0.f, 0.f};
   for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < 2 * g.Nh; e += gridDim.x * blockDim.x) {
     const int p = e >= g.Nh, h = e - p * g.Nh;
-    int x, y, z, t, nb[8];
+    int x, y, z, t, hf, hb;
     site_coords(g, p, h, x, y, z, t);
-    site_neighbors(g, h, x, y, z, t, nb);
-    for (int b = 0; b < cin; ++b) {
-      Cx<float> v[12];
-      transport<R>(g, links, in + b * vstride, p, h, nb, k, v);
-      for (int a = 0; a < cout; ++a) {
+    neighbors_of(g, h, x, y, z, t, mu, hf, hb);
+    Cx<float> u[3][3];
+    if (k >= 5) LinkIO<OVL_F32, R>::load(links, mu, 1 - p, hb, g.Nh, u);
+    else if (k >= 1) LinkIO<OVL_F32, R>::load(links, mu, p, h, g.Nh, u);
+    const int q = k == 0 ? p : 1 - p, hn = k == 0 ? h : k <= 4 ? hf : hb;
+#pragma unroll
+    for (int b = 0; b < CIN; ++b) {
+      Cx<float> s[12], v[12];
+      SpinorIO<OVL_F32>::load(in + b * vstride, q, hn, g.Nh, s);
+      if (k >= 5) colour_mul12<R, true>(u, s, v);
+      else if (k >= 1) colour_mul12<R, false>(u, s, v);
+      else {
+#pragma unroll
+        for (int c = 0; c < 12; ++c) v[c] = s[c];
+      }
+#pragma unroll
+      for (int a = 0; a < COUT; ++a) {
         Cx<float> go[12];
         SpinorIO<OVL_F32>::load(gout + a * vstride, p, h, g.Nh, go);
-        const int base = (a * cin + b) * 16;
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
+        for (int r = 0; r < 4; ++r)
 #pragma unroll
           for (int tt = 0; tt < 4; ++tt) {
-            Cx<float> r = acc[base + 4 * s + tt];
+            Cx<float> z = acc.c[(a * CIN + b) * 16 + 4 * r + tt];
 #pragma unroll
-            for (int c = 0; c < 3; ++c) r = r + cmul_conj(v[3 * tt + c], go[3 * s + c]);
-            acc[base + 4 * s + tt] = r;
+            for (int c = 0; c < 3; ++c) z = z + rounded_mul<true, false>(v[3 * tt + c], go[3 * r + c]);
+            acc.c[(a * CIN + b) * 16 + 4 * r + tt] = z;
           }
       }
+      if (CIN > 1) __builtin_amdgcn_sched_barrier(0);  // one input channel's operands at a time
     }
   }
-  // cmul_conj(v, go) = conj(v) * go, i.e. go * conj(v) as required
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  for (int i = 0; i < nout; ++i) {
-    float re = acc[i].re, im = acc[i].im;
+  int base = 0;
+  wave_deal<2 * NC, 32>(acc.f, lane, base);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      re += __shfl_xor(re, o, 64);
-      im += __shfl_xor(im, o, 64);
-    }
-    if (lane == 0) red[wv][i] = make_float2(re, im);
-  }
+  for (int i = 0; i < dealt(2 * NC); ++i) reinterpret_cast<float*>(red[wv])[base + i] = acc.f[i];
   __syncthreads();
-  for (int i = threadIdx.x; i < nout; i += blockDim.x) {
+  for (int i = threadIdx.x; i < NC; i += blockDim.x) {
     double re = 0.0, im = 0.0;
     for (int w = 0; w < 256 / 64; ++w) {
       re += red[w][i].x;
       im += red[w][i].y;
     }
-    partial[(static_cast<size_t>(k) * gridDim.x + blockIdx.x) * nout + i] = make_double2(re, im);
+    partial[(static_cast<size_t>(k) * gridDim.x + blockIdx.x) * NC + i] = make_double2(re, im);
   }
 }
 
-// out[k][i] (+)= sum_b partial[k][b][i], blocks in order.
-__global__ void wgrad_reduce_kernel(int nout, int G, const double2* partial, double2* out, int accumulate) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int k = blockIdx.y;
-  if (i >= nout) return;
+// out[k][i] (+)= sum_b partial[k][b][i]: 64 sums of every 64th block each,
+// added pairwise (one thread per sum took 64 us).
+__global__ __launch_bounds__(256) void wgrad_reduce_kernel(int nout, int G, const double2* partial, double2* out,
+                                                           int accumulate) {
+  __shared__ double2 red[64][4];
+  const int il = threadIdx.x & 3, bl = threadIdx.x >> 2;
+  const int i = blockIdx.x * 4 + il, k = blockIdx.y;
   double re = 0.0, im = 0.0;
-  for (int b = 0; b < G; ++b) {
-    const double2 v = partial[(static_cast<size_t>(k) * G + b) * nout + i];
-    re += v.x;
-    im += v.y;
+  if (i < nout)
+    for (int b = bl; b < G; b += 64) {
+      const double2 v = partial[(static_cast<size_t>(k) * G + b) * nout + i];
+      re += v.x;
+      im += v.y;
+    }
+  red[bl][il] = make_double2(re, im);
+  for (int o = 32; o > 0; o >>= 1) {
+    __syncthreads();
+    if (bl < o) {
+      re += red[bl + o][il].x;
+      im += red[bl + o][il].y;
+      red[bl][il] = make_double2(re, im);
+    }
   }
-  double2* o = out + static_cast<size_t>(k) * nout + i;
-  if (accumulate) {
-    re += o->x;
-    im += o->y;
+  if (bl == 0 && i < nout) {
+    double2* o = out + static_cast<size_t>(k) * nout + i;
+    if (accumulate) {
+      re += o->x;
+      im += o->y;
+    }
+    *o = make_double2(re, im);
   }
-  *o = make_double2(re, im);
 }
 
 // loss[0] += d2[0] / x2[0];  gscale = (2 / x2[0], 0): the gradient of
@@ -202,6 +345,17 @@ __global__ void pair_loss_kernel(const double* d2, const double* x2, double* los
 }
 
 constexpr int WG_BLOCKS = 256;
+
+// f(integral_constant<CIN>, integral_constant<COUT>) for run-time counts.
+template <int I = 1, class F>
+void with_channel(int n, F&& f) {
+  if constexpr (I <= CMAX) {
+    if (n == I) f(std::integral_constant<int, I>{});
+    else with_channel<I + 1>(n, f);
+  } else {
+    throw Error(OVL_E_ARG, "channels must be 1..4");
+  }
+}
 
 using zc = std::complex<double>;
 
@@ -239,27 +393,41 @@ struct Layer {
     const Geo& g = u->geom.geo;
     dim3 grid((2 * g.Nh + 255) / 256, nb);
     const size_t ri = vstride * cin, ro = vstride * cout;
-    if (recon == 18)
-      hipLaunchKernelGGL(ptc_forward_kernel<18>, grid, dim3(256), 0, s, g, links, static_cast<const char*>(in),
-                         static_cast<char*>(out), vstride, cin, cout, W, ri, ro);
-    else
-      hipLaunchKernelGGL(ptc_forward_kernel<12>, grid, dim3(256), 0, s, g, links, static_cast<const char*>(in),
-                         static_cast<char*>(out), vstride, cin, cout, W, ri, ro);
+    with_channel(cin, [&](auto ci) {
+      with_channel(cout, [&](auto co) {
+        constexpr int CI = decltype(ci)::value, CO = decltype(co)::value;
+        auto go = [&](auto kernel) {
+          hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, g, links, static_cast<const char*>(in),
+                             static_cast<char*>(out), vstride, W, ri, ro);
+        };
+        if (recon == 18) go(ptc_forward_kernel<18, CI, CO>);
+        else go(ptc_forward_kernel<12, CI, CO>);
+      });
+    });
     OVL_HIP(hipGetLastError());
   }
   void wgrad(const void* in, const void* gout, int cin, int cout, double2* out, int accumulate = 0) const {
     const Geo& g = u->geom.geo;
     const int nout = cin * cout * 16;
-    WsBuf part(static_cast<size_t>(NPATH) * WG_BLOCKS * nout * sizeof(double2), s);
-    dim3 grid(WG_BLOCKS, NPATH);
-    if (recon == 18)
-      hipLaunchKernelGGL(ptc_wgrad_kernel<18>, grid, dim3(256), 0, s, g, links, static_cast<const char*>(in),
-                         static_cast<const char*>(gout), vstride, cin, cout, static_cast<double2*>(part.p));
-    else
-      hipLaunchKernelGGL(ptc_wgrad_kernel<12>, grid, dim3(256), 0, s, g, links, static_cast<const char*>(in),
-                         static_cast<const char*>(gout), vstride, cin, cout, static_cast<double2*>(part.p));
+    constexpr int G = WG_BLOCKS;
+    WsBuf part(static_cast<size_t>(NPATH) * G * nout * sizeof(double2), s);
+    with_channel(cin, [&](auto ci) {
+      with_channel(cout, [&](auto co) {
+        constexpr int CI = decltype(ci)::value, CO = decltype(co)::value;
+        if constexpr (CI * CO <= CMAX) {
+          auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(G, NPATH), dim3(256), 0, s, g, links, static_cast<const char*>(in),
+                               static_cast<const char*>(gout), vstride, static_cast<double2*>(part.p));
+          };
+          if (recon == 18) go(ptc_wgrad_kernel<18, CI, CO>);
+          else go(ptc_wgrad_kernel<12, CI, CO>);
+        } else {
+          throw Error(OVL_E_ARG, "weight gradient: cin*cout <= 4");
+        }
+      });
+    });
     OVL_HIP(hipGetLastError());
-    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((nout + 255) / 256, NPATH), dim3(256), 0, s, nout, WG_BLOCKS,
+    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((nout + 3) / 4, NPATH), dim3(256), 0, s, nout, G,
                        static_cast<const double2*>(part.p), out, accumulate);
     OVL_HIP(hipGetLastError());
   }

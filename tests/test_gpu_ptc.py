@@ -66,6 +66,37 @@ def test_layer_forward_and_backward(setup, cin, cout):
     assert gu.rel_err(gW, want_W) < 1e-4
 
 
+@pytest.mark.parametrize("c12", [0, 1])
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (6, 6, 6, 10)])
+def test_layer_channel_counts(dims, c12):
+    """Every channel count the kernels are built for (all of 1..4 x 1..4 forward,
+    products up to 4 backward), with fewer sites than a wave (2^4) and a last
+    block that is not full, several blocks of the weight gradient and an odd
+    number of values per lane in its wave sum (3 channels), on 18- and 12-real
+    links."""
+    lat = Lattice(dims)
+    U = si.gauge_field(dims, 0.3, 12)
+    g = ovl.Geometry(dims)
+    gauge = gu.make_gauge(g, U, [(F32, c12)])
+    phi = np.stack([si.gaussian_spinor(dims, 140 + i) for i in range(4)])
+    gout = np.stack([si.gaussian_spinor(dims, 150 + i) for i in range(4)])
+    for cin in range(1, 5):
+        for cout in range(1, 5):
+            W = np.ascontiguousarray(_w(cin * 10 + cout, cout, cin))
+            out = gu.empty_field(g, F32, cout)
+            din = gu.pack(g, phi[:cin], F32, cin)
+            ovl.ovl_ptc_layer_forward(gauge, din, cin, out, cout, W, None)
+            got = gu.unpack(g, out, F32, cout).reshape(cout, g.N, 4, 3)
+            assert gu.rel_err(got, ptc.forward(lat, U, W, phi[:cin])) < 2e-6, (cin, cout)
+            if cin * cout > 4:
+                continue
+            gin, gW = gu.empty_field(g, F32, cin), np.zeros_like(W)
+            ovl.ovl_ptc_layer_backward(gauge, din, cin, gu.pack(g, gout[:cout], F32, cout), cout, W, gin, gW, None)
+            want_in, want_W = ptc.backward(lat, U, W, phi[:cin], gout[:cout])
+            assert gu.rel_err(gu.unpack(g, gin, F32, cin).reshape(cin, g.N, 4, 3), want_in) < 2e-6, (cin, cout)
+            assert gu.rel_err(gW, want_W) < 1e-4, (cin, cout)
+
+
 def _harvest(g, gauge, U, dims, cap):
     from oracle import dense  # noqa: F401
     s = ovl.Sign(0.4, 6.6, n=60)
