@@ -203,7 +203,7 @@ __device__ inline void turn(double2 (&x)[4]) {
   __builtin_memcpy(x, d, sizeof(d));
 }
 
-// The second sweep.  MODE 0: Y_r = sum_i V_i K_ir, 1: Y_r += the same,
+// The second sweep.  MODE 0: Y_r = f sum_i V_i K_ir, 1: Y_r += the same,
 // 2: psi_h = psi - sum_i C_i V_i into Y and w = [gamma5] sum_i s_i C_i V_i.
 // A block of four waves makes the 16-byte output blocks u of 256 / cpb sites of
 // one parity; a wave the 64 sites of one complex row, four tiles of 16 sites,
@@ -221,7 +221,7 @@ template <int P, int NT, int MODE>
 __global__ __launch_bounds__(256) void sweep_kernel(int Nh, int ell, const char* V, size_t vstrideV, const char* in,
                                                     char* Y, char* w, size_t vstrideP, int R,
                                                     const double2* __restrict__ coef, const int* __restrict__ order,
-                                                    int nsp, int ns, int g5w) {
+                                                    int nsp, int ns, int g5w, double f) {
   constexpr int cpb = Prec<P>::cpb, NB = 12 / cpb, SG = 256 / cpb;  // sites per block
   constexpr int LD = 8 * NT + 9;  // padded row of the LDS exchange: 16 or 24 columns are used
   using real = typename Prec<P>::real;
@@ -363,7 +363,7 @@ __global__ __launch_bounds__(256) void sweep_kernel(int Nh, int ell, const char*
   } else {
     sum(0, ns, acc);
     park();
-    store(MODE == 1 ? Y : nullptr, Y, 1.0, false);
+    store(MODE == 1 ? Y : nullptr, Y, f, false);
   }
 }
 
@@ -450,13 +450,13 @@ void dot_prec(const ovl_geom* g, const void* V, int ell, const void* psi, int pr
 
 template <int P, int MODE>
 void sweep_go(const ovl_geom* g, const void* V, int ell, const void* in, void* Y, void* w, int R, const double2* K,
-              const int* order, int nsp, int ns, int g5w, hipStream_t s) {
+              const int* order, int nsp, int ns, int g5w, double f, hipStream_t s) {
   constexpr int cpb = Prec<P>::cpb;
   const int Nh = g->geo.Nh, blocks = 2 * (12 / cpb) * ((Nh + 256 / cpb - 1) / (256 / cpb));
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, Nh, ell, static_cast<const char*>(V),
                        spinor_vec_bytes(g, OVL_F64), static_cast<const char*>(in), static_cast<char*>(Y),
-                       static_cast<char*>(w), spinor_vec_bytes(g, P), R, K, order, nsp, ns, g5w);
+                       static_cast<char*>(w), spinor_vec_bytes(g, P), R, K, order, nsp, ns, g5w, f);
   };
   if (R <= 8) go(sweep_kernel<P, 1, MODE>);
   else go(sweep_kernel<P, 2, MODE>);
@@ -465,12 +465,12 @@ void sweep_go(const ovl_geom* g, const void* V, int ell, const void* in, void* Y
 
 template <int MODE>
 void sweep_prec(const ovl_geom* g, const void* V, int ell, const void* in, void* Y, void* w, int prec, int R,
-                const double2* K, const int* order, int nsp, int ns, int g5w, hipStream_t s) {
+                const double2* K, const int* order, int nsp, int ns, int g5w, double f, hipStream_t s) {
   switch (prec) {
-    case OVL_F64: sweep_go<OVL_F64, MODE>(g, V, ell, in, Y, w, R, K, order, nsp, ns, g5w, s); break;
-    case OVL_F32: sweep_go<OVL_F32, MODE>(g, V, ell, in, Y, w, R, K, order, nsp, ns, g5w, s); break;
-    case OVL_F16: sweep_go<OVL_F16, MODE>(g, V, ell, in, Y, w, R, K, order, nsp, ns, g5w, s); break;
-    case OVL_BF16: sweep_go<OVL_BF16, MODE>(g, V, ell, in, Y, w, R, K, order, nsp, ns, g5w, s); break;
+    case OVL_F64: sweep_go<OVL_F64, MODE>(g, V, ell, in, Y, w, R, K, order, nsp, ns, g5w, f, s); break;
+    case OVL_F32: sweep_go<OVL_F32, MODE>(g, V, ell, in, Y, w, R, K, order, nsp, ns, g5w, f, s); break;
+    case OVL_F16: sweep_go<OVL_F16, MODE>(g, V, ell, in, Y, w, R, K, order, nsp, ns, g5w, f, s); break;
+    case OVL_BF16: sweep_go<OVL_BF16, MODE>(g, V, ell, in, Y, w, R, K, order, nsp, ns, g5w, f, s); break;
     default: throw Error(OVL_E_PRECISION, "unknown precision");
   }
 }
@@ -489,8 +489,40 @@ void block_axpy(const ovl_geom* g, const void* V, int ell, const double2* K, voi
                 hipStream_t s) {
   OVL_REQUIRE(R >= 1 && R <= OVL_MAX_RHS && ell >= 1, OVL_E_ARG, "block_axpy: 1 <= R <= 12, ell >= 1");
   const int ns = (ell + 3) / 4;
-  if (keep) sweep_prec<1>(g, V, ell, nullptr, Y, nullptr, prec, R, K, nullptr, ns, ns, 0, s);
-  else sweep_prec<0>(g, V, ell, nullptr, Y, nullptr, prec, R, K, nullptr, ns, ns, 0, s);
+  if (keep) sweep_prec<1>(g, V, ell, nullptr, Y, nullptr, prec, R, K, nullptr, ns, ns, 0, 1.0, s);
+  else sweep_prec<0>(g, V, ell, nullptr, Y, nullptr, prec, R, K, nullptr, ns, ns, 0, 1.0, s);
+}
+
+namespace {
+// coef = c1 + c2, beta = sqrt(n2), inv = 1 / beta (as a complex scalar).
+__global__ void lanczos_scalars_kernel(int n, const double2* c1, const double2* c2, double2* coef, const double* n2,
+                                       double* beta, double* inv) {
+  for (int i = threadIdx.x; i < n; i += blockDim.x) coef[i] = make_double2(c1[i].x + c2[i].x, c1[i].y + c2[i].y);
+  if (threadIdx.x == 0) {
+    const double b = sqrt(n2[0]);
+    beta[0] = b;
+    inv[0] = 1.0 / b;
+    inv[1] = 0.0;
+  }
+}
+}  // namespace
+
+// Nothing of a step needs the host: coefficients, norm and scale stay on the
+// device (six synchronisations a step, 0.1 ms, on the host before).
+void lanczos_step(const ovl_geom* g, const void* Q, int n, void* w, void* next, double2* coef, double* beta,
+                  double2* scratch, hipStream_t s) {
+  double2 *c1 = scratch, *c2 = scratch + n;
+  double* sc = reinterpret_cast<double*>(scratch + 2 * n);  // norm (2), 1 / beta (2)
+  const size_t v64 = spinor_vec_bytes(g, OVL_F64);
+  const int ns = (n + 3) / 4;
+  for (double2* c : {c1, c2}) {
+    block_dot(g, Q, n, w, OVL_F64, 1, c, s);
+    sweep_prec<1>(g, Q, n, nullptr, w, nullptr, OVL_F64, 1, c, nullptr, ns, ns, 0, -1.0, s);
+  }
+  blas_norm2(OVL_F64, v64 / 16, w, 1, v64, sc, s);
+  hipLaunchKernelGGL(lanczos_scalars_kernel, dim3(1), dim3(256), 0, s, n, c1, c2, coef, sc, beta, sc + 2);
+  OVL_HIP(hipGetLastError());
+  blas_axpby(OVL_F64, w, sc + 2, OVL_F64, next, nullptr, static_cast<size_t>(g->N), 1, s);
 }
 
 void block_rotate_inplace(const ovl_geom* g, void* V, int K, const double2* S, int k, hipStream_t s) {
@@ -513,7 +545,7 @@ void lowmode_project_ws(const ovl_lowmodes* lm, const void* psi, void* psih, voi
               "projection: 1 <= nrhs <= 12 and at least one low mode");
   dot_prec(&lm->geom, lm->V, lm->ell, psi, prec, nrhs, C, part, G, s);
   sweep_prec<2>(&lm->geom, lm->V, lm->ell, psi, psih, w, prec, nrhs, C, lm->dev_order, lm->steps_pos, lm->steps, g5w,
-                s);
+                1.0, s);
 }
 
 // Scratch of the allocation-free projection: one array per GPU, in device

@@ -79,6 +79,12 @@ void block_dot(const ovl_geom* g, const void* V, int ell, const void* psi, int p
                hipStream_t s);
 void block_axpy(const ovl_geom* g, const void* V, int ell, const double2* K, void* Y, int prec, int R, bool keep,
                 hipStream_t s);
+// One Lanczos step's vector work, all on the stream: w -= Q (Q^dag w) twice for
+// the n FP64 vectors Q, coef[0..n) = the two passes' coefficients added, beta =
+// ||w||, next = w / beta.  scratch: 2n + 2 complex numbers.  coef, beta and
+// scratch are device memory.
+void lanczos_step(const ovl_geom* g, const void* Q, int n, void* w, void* next, double2* coef, double* beta,
+                  double2* scratch, hipStream_t s);
 // In place: V[:, j] = sum_{i<K} V[:, i] S[i + K*j] for j < k (FP64 basis, S on the device, K <= 512).
 void block_rotate_inplace(const ovl_geom* g, void* V, int K, const double2* S, int k, hipStream_t s);
 
