@@ -525,6 +525,84 @@ void lanczos_step(const ovl_geom* g, const void* Q, int n, void* w, void* next, 
   blas_axpby(OVL_F64, w, sc + 2, OVL_F64, next, nullptr, static_cast<size_t>(g->N), 1, s);
 }
 
+namespace {
+// The scalars of lanczos_fused from D[R i] = s_i = q_i^dag u, D[R i + 1] = t_i =
+// q_i^dag y (i < j), D[R j] = u^dag u, D[R j + 1] = u^dag y; R = 1: there is no y.
+template <int R>
+__global__ __launch_bounds__(256) void lanczos_fused_scalars_kernel(int j, const double2* D, double* alpha,
+                                                                    double* beta, double* sc) {
+  double v[3] = {0.0, 0.0, 0.0};  // s^dag s, s^dag t
+  for (int i = threadIdx.x; i < j; i += 256) {
+    const double2 a = D[R * i], b = D[R * i + R - 1];
+    v[0] += a.x * a.x + a.y * a.y;
+    v[1] += a.x * b.x + a.y * b.y;
+    v[2] += a.x * b.y - a.y * b.x;
+  }
+  __shared__ double red[3][256];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) red[k][threadIdx.x] = v[k];
+  for (int o = 128; o > 0; o >>= 1) {
+    __syncthreads();
+    if (threadIdx.x < o)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + o];
+  }
+  if (threadIdx.x) return;
+  double b2 = D[R * j].x - red[0][0];
+  if (b2 < 0.0) b2 = 0.0;  // rounding; a NaN stays
+  const double b = sqrt(b2), last = j > 0 ? D[R * (j - 1)].x : 0.0;  // s_{j-1}
+  if (j > 0) {
+    alpha[j - 1] += last;
+    beta[j - 1] = b;
+  }
+  if constexpr (R == 2) {
+    const double2 uy = D[2 * j + 1];
+    const double pr = (uy.x - red[1][0]) / b2, pi = (uy.y - red[2][0]) / b2;  // q_j^dag y / beta
+    alpha[j] = pr - last;
+    sc[0] = 1.0 / b;
+    sc[1] = pr;
+    sc[2] = pi;
+  }
+}
+
+// u *= c, y = c y - (p + i q) u (the new one) for sc = {c, p, q}.
+__global__ __launch_bounds__(256) void lanczos_next_kernel(size_t n, const double* sc, double2* u, double2* y) {
+  const double c = sc[0], p = sc[1], q = sc[2];
+  for (size_t i = blockIdx.x * 256ul + threadIdx.x; i < n; i += gridDim.x * 256ul) {
+    const double2 a = u[i], b = y[i], z = make_double2(c * a.x, c * a.y);
+    u[i] = z;
+    y[i] = make_double2(c * b.x - (p * z.x - q * z.y), c * b.y - (p * z.y + q * z.x));
+  }
+}
+}  // namespace
+
+// With q = (u - Q s) / beta, beta^2 = u^dag u - s^dag s, and y = H u: q_j^dag y =
+// (u^dag y - s^dag t) / beta, and (y - Q t - q q_j^dag y) / beta is H q without its
+// parts along Q and q, because H Q s lies in their span; along q it has beta
+// s_{j-1} (the recurrence), so q_j^dag H q = q_j^dag y / beta - s_{j-1}.  One step's second
+// pass and the next step's first pass are then one reading of Q for the dots and
+// one for the updates; lanczos_step reads it four times.  Bound by those readings,
+// 92 GB for 60 steps at 16^3x32: ovl_hw_bound 39.6 ms with four, 23.3 ms now.
+void lanczos_fused(const ovl_geom* g, void* Q, int j, bool last, double* alpha, double* beta, double2* scratch,
+                   hipStream_t s) {
+  const size_t v64 = spinor_vec_bytes(g, OVL_F64);
+  char* u = static_cast<char*>(Q) + static_cast<size_t>(j) * v64;
+  double* sc = reinterpret_cast<double*>(scratch + 2 * (j + 1));
+  auto scalars = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(1), dim3(256), 0, s, j, scratch, alpha, beta, sc);
+    OVL_HIP(hipGetLastError());
+  };
+  block_dot(g, Q, j + 1, u, OVL_F64, last ? 1 : 2, scratch, s);
+  if (last) return scalars(lanczos_fused_scalars_kernel<1>);
+  scalars(lanczos_fused_scalars_kernel<2>);
+  const int ns = (j + 3) / 4;
+  if (j > 0) sweep_prec<1>(g, Q, j, nullptr, u, nullptr, OVL_F64, 2, scratch, nullptr, ns, ns, 0, -1.0, s);
+  const size_t n = v64 / 16;
+  hipLaunchKernelGGL(lanczos_next_kernel, dim3(static_cast<unsigned>(std::min<size_t>((n + 255) / 256, 8192))),
+                     dim3(256), 0, s, n, sc, reinterpret_cast<double2*>(u), reinterpret_cast<double2*>(u + v64));
+  OVL_HIP(hipGetLastError());
+}
+
 void block_rotate_inplace(const ovl_geom* g, void* V, int K, const double2* S, int k, hipStream_t s) {
   OVL_REQUIRE(k >= 1 && k <= K, OVL_E_ARG, "rotate: need 1 <= k <= K");
   const size_t lds = static_cast<size_t>(K) * RT * sizeof(Cx<double>);

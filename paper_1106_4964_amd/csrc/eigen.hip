@@ -270,9 +270,8 @@ int ovl_hw_bound(const ovl_gauge* u, double rho, const void* v0, int steps, doub
     H.links = gauge_links(u, OVL_F64, &H.recon);
     const size_t v64 = H.v64;
     DevMem Q(v64 * (steps + 1));
-    WsBuf w(v64, s), sc(4 * sizeof(double), s), cb(sizeof(double2) * (2 * steps + 2), s);
-    // coefficients (row j: j + 1 of them) and norms of every step, read at the end
-    WsBuf cf(sizeof(double2) * steps * steps, s), bt(sizeof(double) * steps, s);
+    WsBuf sc(4 * sizeof(double), s), cb(sizeof(double2) * (2 * steps + 4), s);
+    WsBuf ab(2 * sizeof(double) * steps, s);  // alpha, beta, read at the end
     // q0 = v0 / ||v0||
     auto norm = [&](const void* x) {
       blas_norm2(OVL_F64, v64 / 16, x, 1, v64, static_cast<double*>(sc.p), s);
@@ -290,19 +289,18 @@ int ovl_hw_bound(const ovl_gauge* u, double rho, const void* v0, int steps, doub
     const double n0 = norm(v0);
     OVL_REQUIRE(n0 > 0.0 && std::isfinite(n0), OVL_E_ARG, "start vector is zero or not finite");
     scale_into(vec(Q.p, v64, 0), v0, 1.0 / n0);
+    // full re-orthogonalisation (twice); the last pass finds the last beta
+    double *da = static_cast<double*>(ab.p), *db = da + steps;
     for (int j = 0; j < steps; ++j) {
-      H.apply(w.p, vec(Q.p, v64, j), 1);
-      // full re-orthogonalisation (twice): w -= Q (Q^dag w); alpha_j = q_j^dag w
-      lanczos_step(g, Q.p, j + 1, w.p, vec(Q.p, v64, j + 1), static_cast<double2*>(cf.p) + static_cast<size_t>(j) * steps,
-                   static_cast<double*>(bt.p) + j, static_cast<double2*>(cb.p), s);
+      H.apply(vec(Q.p, v64, j + 1), vec(Q.p, v64, j), 1);
+      lanczos_fused(g, Q.p, j, false, da, db, static_cast<double2*>(cb.p), s);
     }
+    lanczos_fused(g, Q.p, steps, true, da, db, static_cast<double2*>(cb.p), s);
     std::vector<double> alpha(steps), beta(steps);
-    std::vector<double2> hc(static_cast<size_t>(steps) * steps);
-    OVL_HIP(hipMemcpyAsync(hc.data(), cf.p, sizeof(double2) * steps * steps, hipMemcpyDeviceToHost, s));
-    OVL_HIP(hipMemcpyAsync(beta.data(), bt.p, sizeof(double) * steps, hipMemcpyDeviceToHost, s));
+    OVL_HIP(hipMemcpyAsync(alpha.data(), da, sizeof(double) * steps, hipMemcpyDeviceToHost, s));
+    OVL_HIP(hipMemcpyAsync(beta.data(), db, sizeof(double) * steps, hipMemcpyDeviceToHost, s));
     OVL_HIP(hipStreamSynchronize(s));
     for (int j = 0; j < steps; ++j) {
-      alpha[j] = hc[static_cast<size_t>(j) * steps + j].x;
       if (beta[j] < 1e-14 * std::fabs(alpha[j])) {  // invariant subspace: the later steps mean nothing
         alpha.resize(j + 1);
         beta.resize(j + 1);

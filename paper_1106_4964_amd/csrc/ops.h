@@ -85,6 +85,14 @@ void block_axpy(const ovl_geom* g, const void* V, int ell, const double2* K, voi
 // scratch are device memory.
 void lanczos_step(const ovl_geom* g, const void* Q, int n, void* w, void* next, double2* coef, double* beta,
                   double2* scratch, hipStream_t s);
+// The same for a basis from one start vector, with the second pass on a step's
+// vector left to the next step.  On entry Q holds q_0 .. q_{j-1}, u (orthogonal
+// to them by one pass, not normalised) and y = H u; on exit q_j for u and the
+// next u for y, beta[j-1] = the norm of u after its second pass, alpha[j-1]
+// complete and alpha[j] without its second pass.  last: there is no y, and only
+// alpha[j-1] and beta[j-1] are formed.  scratch: 2 (j + 1) + 2 complex.
+void lanczos_fused(const ovl_geom* g, void* Q, int j, bool last, double* alpha, double* beta, double2* scratch,
+                   hipStream_t s);
 // In place: V[:, j] = sum_{i<K} V[:, i] S[i + K*j] for j < k (FP64 basis, S on the device, K <= 512).
 void block_rotate_inplace(const ovl_geom* g, void* V, int K, const double2* S, int k, hipStream_t s);
 
