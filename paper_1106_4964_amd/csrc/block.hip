@@ -367,6 +367,107 @@ __global__ __launch_bounds__(256) void sweep_kernel(int Nh, int ell, const char*
   }
 }
 
+// The same for one or two vectors, with FP64 FMAs: a thread is a site and one of
+// its 16-byte blocks of rows, and reads U modes ahead.  Bound by the basis: 8 FMAs
+// or fewer per 16 bytes need no matrix instruction, and without the LDS turn five
+// to six waves a SIMD fit instead of three.  Both readings together, one vector
+// (two), with sweep_kernel and with this: 16^3x32, 50 modes, F16 425 -> 406 us
+// (441 -> 418), FP32 445 -> 426 (460 -> 440), FP64 465 -> 460 (472 -> 471);
+// 24^3x64, 100 modes, F16 5.44 -> 5.39 ms, FP64 5.95 -> 5.91.
+template <int P, int R, int MODE>
+__global__ __launch_bounds__(256) void sweep_small_kernel(int Nh, int ell, const char* V, size_t vstrideV,
+                                                          const char* in, char* Y, char* w, size_t vstrideP,
+                                                          const double2* __restrict__ coef,
+                                                          const int* __restrict__ order, int nsp, int ns, int g5w,
+                                                          double f) {
+  constexpr int cpb = Prec<P>::cpb, NB = 12 / cpb, U = cpb == 1 ? 8 : cpb == 2 ? 4 : 2;
+  using real = typename Prec<P>::real;
+  const int h = blockIdx.x * 256 + threadIdx.x, pu = blockIdx.y;  // pu = p NB + u
+  if (h >= Nh) return;
+  V += static_cast<size_t>(pu * cpb) * Nh * 16;
+  const uint32_t hoff = static_cast<uint32_t>(h) * 16u;
+  Cx<double> acc[2][R][cpb];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int c = 0; c < cpb; ++c) acc[0][r][c] = acc[1][r][c] = {0.0, 0.0};
+  auto sum = [&](int k0, int k1, Cx<double> (*a)[cpb]) {
+    if (MODE == 2)
+      while (k1 > k0 && order[k1 - 1] < 0) --k1;  // the padding of the last quad
+    auto mode = [&](int k) { return MODE == 2 ? order[k] : k; };
+    Cx<double> va[2][U][cpb];
+    auto request = [&](int d, int k) {
+#pragma unroll
+      for (int m = 0; m < U; ++m) {
+        const char* v = V + static_cast<size_t>(mode(min(k + m, k1 - 1))) * vstrideV;
+#pragma unroll
+        for (int c = 0; c < cpb; ++c) va[d][m][c] = load_basis_at(v + static_cast<size_t>(c) * Nh * 16 + hoff);
+      }
+    };
+    auto use = [&](int d, int k) {
+#pragma unroll
+      for (int m = 0; m < U; ++m) {
+        if (k + m >= k1) break;
+        const double2* cm = coef + mode(k + m) * R;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+          for (int c = 0; c < cpb; ++c) {
+            Cx<double>& x = a[r][c];
+            const Cx<double> v = va[d][m][c];
+            x.re = fma(v.re, cm[r].x, x.re);
+            x.im = fma(v.re, cm[r].y, x.im);
+            x.re = fma(-v.im, cm[r].y, x.re);
+            x.im = fma(v.im, cm[r].x, x.im);
+          }
+      }
+    };
+    if (k0 >= k1) return;
+    request(0, k0);
+    for (int k = k0; k < k1; k += 2 * U) {
+#pragma unroll
+      for (int d = 0; d < 2; ++d) {
+        request(1 - d, k + (d + 1) * U);
+        __builtin_amdgcn_sched_barrier(0);
+        use(d, k + d * U);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+  const size_t off = (static_cast<size_t>(pu) * Nh + h) * 16;
+  auto store = [&](const char* base, char* out, Cx<double> (*a)[cpb], double sgn, bool lower) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      Cx<real> y[cpb];
+      if (base) Block<P>::load(base + r * vstrideP + off, y);
+#pragma unroll
+      for (int c = 0; c < cpb; ++c) {
+        const double g = (lower && (pu % NB) * cpb + c >= 6) ? -sgn : sgn;
+        const double b0 = base ? static_cast<double>(y[c].re) : 0.0, b1 = base ? static_cast<double>(y[c].im) : 0.0;
+        y[c] = {static_cast<real>(b0 + g * a[r][c].re), static_cast<real>(b1 + g * a[r][c].im)};
+      }
+      Block<P>::store(out + r * vstrideP + off, y);
+    }
+  };
+  if constexpr (MODE == 2) {
+    sum(0, 4 * nsp, acc[0]);
+    sum(4 * nsp, 4 * ns, acc[1]);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int c = 0; c < cpb; ++c) {
+        const Cx<double> a = acc[0][r][c], b = acc[1][r][c];
+        acc[0][r][c] = a + b;
+        acc[1][r][c] = a - b;
+      }
+    store(in, Y, acc[0], -1.0, false);
+    store(nullptr, w, acc[1], 1.0, g5w != 0);
+  } else {
+    sum(0, ell, acc[0]);
+    store(MODE == 1 ? Y : nullptr, Y, acc[0], f, false);
+  }
+}
+
 // In-place basis rotation V[:, j] = sum_{i<K} V[:, i] S[i + K j], j < k.
 // Each block stages all K values of RT consecutive elements of one row in
 // LDS, so every element is read once and rewritten by the same block.
@@ -458,7 +559,15 @@ void sweep_go(const ovl_geom* g, const void* V, int ell, const void* in, void* Y
                        spinor_vec_bytes(g, OVL_F64), static_cast<const char*>(in), static_cast<char*>(Y),
                        static_cast<char*>(w), spinor_vec_bytes(g, P), R, K, order, nsp, ns, g5w, f);
   };
-  if (R <= 8) go(sweep_kernel<P, 1, MODE>);
+  auto small = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((Nh + 255) / 256, 24 / cpb), dim3(256), 0, s, Nh, ell, static_cast<const char*>(V),
+                       spinor_vec_bytes(g, OVL_F64), static_cast<const char*>(in), static_cast<char*>(Y),
+                       static_cast<char*>(w), spinor_vec_bytes(g, P), K, order, nsp, ns, g5w, f);
+  };
+  if (R <= 2) {  // FMAs do where the matrix instruction would use 2 or 4 of its 16 columns
+    if (R == 1) small(sweep_small_kernel<P, 1, MODE>);
+    else small(sweep_small_kernel<P, 2, MODE>);
+  } else if (R <= 8) go(sweep_kernel<P, 1, MODE>);
   else go(sweep_kernel<P, 2, MODE>);
   OVL_HIP(hipGetLastError());
 }
@@ -508,7 +617,7 @@ __global__ void lanczos_scalars_kernel(int n, const double2* c1, const double2* 
 }  // namespace
 
 // Nothing of a step needs the host: coefficients, norm and scale stay on the
-// device (six synchronisations a step, 0.1 ms, on the host before).
+// device (the host took part six times a step before, about 15 us).
 void lanczos_step(const ovl_geom* g, const void* Q, int n, void* w, void* next, double2* coef, double* beta,
                   double2* scratch, hipStream_t s) {
   double2 *c1 = scratch, *c2 = scratch + n;

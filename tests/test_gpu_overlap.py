@@ -198,3 +198,33 @@ def test_projection_tile_edges(prec, dims):
         for dev, want in ((h, want_h), (w, want_w)):
             got = np.reshape(gu.unpack(g, dev, prec, nrhs), (nrhs, -1))
             assert np.max(np.abs(got - want)) <= tol * max(1.0, np.max(np.abs(want))), (ell, nrhs, signs)
+
+
+@pytest.mark.parametrize("prec", [ovl.OVL_F64, ovl.OVL_F32, ovl.OVL_F16, ovl.OVL_BF16])
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (6, 6, 6, 10)])
+def test_projection_of_few_vectors(prec, dims):
+    """One and two vectors (no matrix instructions in the second reading) and
+    the first batch past them: mode counts around the groups of 2, 4 and 8 that
+    are read ahead, one sign or both, a site range with a remainder."""
+    g = ovl.Geometry(dims)
+    V = si.orthonormal_spinors(dims, 37, 19)
+    vdev = _lowmodes_dev(g, V)
+    Vm = V.reshape(37, -1)
+    psi = np.stack([si.gaussian_spinor(dims, 900 + r) for r in range(3)])
+    u = gu.UNIT_ROUNDOFF[prec]
+    for ell in (1, 2, 3, 8, 9, 16, 17, 37):
+        for nrhs in (1, 2, 3):
+            for npos in {0, 1, ell // 2, ell}:
+                lam = np.where(np.arange(ell) < npos, 0.2, -0.3)[::-1].copy()
+                lm = ovl.LowModes(g, vdev, lam)
+                inp = gu.pack(g, psi[:nrhs], prec, nrhs)
+                h, w = gu.empty_field(g, prec, nrhs), gu.empty_field(g, prec, nrhs)
+                ovl.ovl_lowmodes_project(lm, inp, h, w, prec, nrhs, None)
+                x = np.reshape(gu.unpack(g, inp, prec, nrhs), (nrhs, -1))
+                c = Vm[:ell].conj() @ x.T
+                want_h = x - (Vm[:ell].T @ c).T
+                want_w = (Vm[:ell].T @ (np.sign(lam)[:, None] * c)).T
+                tol = 1e-13 if prec == ovl.OVL_F64 else 2 * u  # FP64 sums, then the storage rounding
+                for dev, want in ((h, want_h), (w, want_w)):
+                    got = np.reshape(gu.unpack(g, dev, prec, nrhs), (nrhs, -1))
+                    assert np.max(np.abs(got - want)) <= tol * max(1.0, np.max(np.abs(want))), (ell, nrhs, npos)
