@@ -42,18 +42,10 @@ HBM_PEAK_GBS = 8000.0
 # stencil configuration: (extra epilogue vectors, tuned shape kr, bs, pipe,
 # rin, tm).  Summary and commands: profiles/stencil_f16_12rhs_24x24x24x64_counters.md
 PROFILED_TRAFFIC = {
-    (3, (2, 128, 0, 0, 0)): 4080216064,
-    (0, (2, 128, 0, 0, 0)): 3094016000,
-    (3, (2, 256, 0, 0, 0)): 4072608000,
-    (0, (2, 256, 0, 0, 0)): 3037061120,
-    (3, (2, 128, 0, 0, 4)): 3638409216,
-    (0, (2, 128, 0, 0, 4)): 2811045888,
-    (3, (2, 128, 0, 0, 8)): 3599534080,
-    (0, (2, 128, 0, 0, 8)): 2698047488,
-    (3, (2, 256, 0, 0, 4)): 3534860288,
-    (0, (2, 256, 0, 0, 4)): 2486437888,
-    (3, (2, 256, 0, 0, 8)): 3578030699,
-    (0, (2, 256, 0, 0, 8)): 2634959975,
+    (3, (3, 256, 0, 0, 8)): 3154659328,
+    (0, (3, 256, 0, 0, 8)): 1597499392,
+    (3, (2, 256, 0, 0, 8)): 3269695488,
+    (0, (2, 256, 0, 0, 8)): 1736337408,
 }
 
 
@@ -781,8 +773,9 @@ def main():
         "unit": "GB/s",
         "frac": round(dom_gbs / HBM_PEAK_GBS, 4),
         "traffic": traffic,
-        "kernel": "stencil_kernel<%s, 12-real links, %d extra vectors>, %d rhs, %s"
-                  % (args.prec.upper(), dom_nv, R, "x".join(map(str, dims))),
+        "kernel": "%s<%s, 12-real links, %d extra vectors>, %d rhs, %s"
+                  % ("stencil_kernel" if dom_shape[3] else "stencil_split_kernel", args.prec.upper(), dom_nv, R,
+                     "x".join(map(str, dims))),
         "bytes_per_launch": dom_bytes,
         "avg_launch_us": round(dom_us, 2),
         "launches": n_dom,
