@@ -46,6 +46,10 @@ PROFILED_TRAFFIC = {
     (0, (3, 256, 0, 0, 8)): 1597499392,
     (3, (2, 256, 0, 0, 8)): 3269695488,
     (0, (2, 256, 0, 0, 8)): 1736337408,
+    (3, (3, 256, 0, 0, 4)): 3197319168,
+    (0, (3, 256, 0, 0, 4)): 1668225024,
+    (3, (2, 256, 0, 0, 4)): 3378061312,
+    (0, (2, 256, 0, 0, 4)): 1849206784,
 }
 
 
