@@ -414,6 +414,9 @@ int ovl_propagator(void* out, const void* x, const ovl_gauge* u, double rho, con
  *   steps.  lam_max = max over the two extreme Ritz pairs of
  *   |theta| + ||H_w y - theta y||: the normalisation ||H_w|| of Q = H_w/||H_w||
  *   (eq. 5).  theta_min/theta_max (may be NULL): the extreme Ritz values.
+ *   Fewer steps are used where v0 lies in a smaller invariant subspace.
+ *   OVL_E_ARG for a zero or non-finite v0, OVL_E_NAN when the recurrence
+ *   meets a NaN or Inf (non-finite links).
  * ovl_hw_eigs: the ell eigenpairs of H_w with smallest |lambda|, for the
  *   projection of eq. 6-7.  Thick-restart Lanczos (FP64, full
  *   re-orthogonalisation) on the Chebyshev polynomial T_degree of H_w^2

@@ -104,14 +104,16 @@ namespace {
 // off-diagonal entry of T - mu starts a bulge, which further rotations chase
 // down the unreduced block; z collects the rotations' action on the last row
 // only.  O(n^2), where Jacobi on the dense matrix took 11 ms for 60 steps.
-void host_tridiag(std::vector<double>& d, std::vector<double>& e, std::vector<double>& z) {
+// False if 60 n sweeps did not separate them.
+bool host_tridiag(std::vector<double>& d, std::vector<double>& e, std::vector<double>& z) {
   const int n = static_cast<int>(d.size());
   z.assign(n, 0.0);
   z[n - 1] = 1.0;
   const double eps = 2.2e-16;
   auto small = [&](int i) { return std::fabs(e[i]) <= eps * (std::fabs(d[i]) + std::fabs(d[i + 1])); };
   int hi = n - 1;
-  for (int it = 0; hi > 0 && it < 60 * n; ++it) {
+  for (int it = 0; hi > 0; ++it) {
+    if (it == 60 * n) return false;
     if (small(hi - 1)) {
       --hi;
       continue;
@@ -140,6 +142,7 @@ void host_tridiag(std::vector<double>& d, std::vector<double>& e, std::vector<do
       z[k + 1] = c * zn - s * zk;
     }
   }
+  return true;
 }
 
 struct Hw {
@@ -300,8 +303,16 @@ int ovl_hw_bound(const ovl_gauge* u, double rho, const void* v0, int steps, doub
     OVL_HIP(hipMemcpyAsync(alpha.data(), da, sizeof(double) * steps, hipMemcpyDeviceToHost, s));
     OVL_HIP(hipMemcpyAsync(beta.data(), db, sizeof(double) * steps, hipMemcpyDeviceToHost, s));
     OVL_HIP(hipStreamSynchronize(s));
+    // A beta at the rounding of H_w q ends the recurrence (an invariant subspace:
+    // what later steps found is noise, or NaN where beta is exactly 0).  The
+    // rounding goes with the terms of H_w q, |4 - rho| from the diagonal and at
+    // most 4 from the hops of unitary links, or with the largest coefficients so
+    // far; alpha_j alone may vanish.
+    double size = std::fabs(4.0 - rho) + 4.0;
     for (int j = 0; j < steps; ++j) {
-      if (beta[j] < 1e-14 * std::fabs(alpha[j])) {  // invariant subspace: the later steps mean nothing
+      OVL_REQUIRE(std::isfinite(alpha[j]) && std::isfinite(beta[j]), OVL_E_NAN, "NaN or Inf in the Lanczos recurrence");
+      size = std::max(size, std::fabs(alpha[j]) + beta[j]);
+      if (beta[j] <= 1e-14 * size) {
         alpha.resize(j + 1);
         beta.resize(j + 1);
         break;
@@ -310,7 +321,7 @@ int ovl_hw_bound(const ovl_gauge* u, double rho, const void* v0, int steps, doub
     const int k = static_cast<int>(alpha.size());
     const double bk = std::fabs(beta[k - 1]);
     std::vector<double> last;  // alpha becomes the Ritz values, last the vectors' components on q_k
-    host_tridiag(alpha, beta, last);
+    OVL_REQUIRE(host_tridiag(alpha, beta, last), OVL_E_BREAKDOWN, "Lanczos: the tridiagonal eigenvalues did not converge");
     int lo = 0, hi = 0;
     for (int i = 1; i < k; ++i) {
       if (alpha[i] < alpha[lo]) lo = i;

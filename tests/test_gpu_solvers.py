@@ -457,3 +457,49 @@ def test_lanczos_bound_ends_in_an_invariant_subspace(dims, steps):
                      ctypes.byref(tmin), ctypes.byref(tmax), None)
     want = (RHO, -RHO, RHO)
     assert np.allclose((lam.value, tmin.value, tmax.value), want, rtol=0, atol=1e-12)
+
+
+@pytest.mark.parametrize("steps", [2, 3, 5, 30])
+@pytest.mark.parametrize("dims,comps", [((4, 4, 4, 4), 12), ((6, 4, 10, 8), 12), ((8, 8, 8, 8), 12),
+                                        ((4, 4, 4, 4), 4), ((4, 4, 8, 8), 4), ((8, 8, 8, 8), 4)])
+def test_lanczos_bound_where_the_diagonal_vanishes(dims, comps, steps):
+    """Free field, constant spinor with equal chiral parts: H_w = -rho gamma_5 on
+    the two-dimensional subspace, so alpha = 0 and beta_1 is rounding, or exactly 0
+    with alpha (4 of the 12 components on 4^k sites: every number is a power of two
+    times rho), which no comparison with alpha can tell.  The Ritz values are -rho
+    and rho."""
+    g = ovl.Geometry(dims)
+    U = np.broadcast_to(np.eye(3, dtype=complex), si.gauge_field(dims, 0.3, 1).shape).copy()
+    psi = np.ones_like(si.gaussian_spinor(dims, 1))
+    if comps == 4:
+        psi[:, 1::2] = 0.0
+        psi[:, :, 2] = 0.0
+    lam, tmin, tmax = ctypes.c_double(), ctypes.c_double(), ctypes.c_double()
+    ovl.ovl_hw_bound(gu.make_gauge(g, U), RHO, gu.pack(g, psi, ovl.OVL_F64), steps, ctypes.byref(lam),
+                     ctypes.byref(tmin), ctypes.byref(tmax), None)
+    assert np.allclose((lam.value, tmin.value, tmax.value), (RHO, -RHO, RHO), rtol=0, atol=1e-12)
+
+
+def test_lanczos_bound_of_the_whole_space():
+    """More steps than 2^4 has dimensions (192): the recurrence ends by itself and
+    the extreme Ritz values are the extreme eigenvalues."""
+    dims = (2, 2, 2, 2)
+    U = si.gauge_field(dims, 0.3, 2)
+    w = np.linalg.eigvalsh(dense.dense_hw(Lattice(dims), U, RHO))
+    g = ovl.Geometry(dims)
+    lam, tmin, tmax = ctypes.c_double(), ctypes.c_double(), ctypes.c_double()
+    ovl.ovl_hw_bound(gu.make_gauge(g, U), RHO, gu.pack(g, si.gaussian_spinor(dims, 3), ovl.OVL_F64), 220,
+                     ctypes.byref(lam), ctypes.byref(tmin), ctypes.byref(tmax), None)
+    assert np.allclose((lam.value, tmin.value, tmax.value), (np.max(np.abs(w)), w[0], w[-1]), rtol=0, atol=1e-12)
+
+
+def test_lanczos_bound_refuses_non_finite_links():
+    dims = (4, 4, 4, 4)
+    U = si.gauge_field(dims, 0.3, 1)
+    U[7, 1, 0, 2] = np.nan
+    g = ovl.Geometry(dims)
+    lam = ctypes.c_double(-1.0)
+    with pytest.raises(ovl.OvlError) as e:
+        ovl.ovl_hw_bound(gu.make_gauge(g, U), RHO, gu.pack(g, si.gaussian_spinor(dims, 3), ovl.OVL_F64), 5,
+                         ctypes.byref(lam), None, None, None)
+    assert e.value.name == "OVL_E_NAN" and lam.value == -1.0
