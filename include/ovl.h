@@ -80,7 +80,7 @@ int ovl_version(void);
 
 /* ---------------------------------------------------------------- geometry
  * Site ordering and neighbours of the periodic lattice (Sec. II, Fig. 1).
- * ovl_geom_create: OVL_E_DIMS if an extent is odd or < 2, or N >= 2^31.
+ * ovl_geom_create: OVL_E_DIMS if an extent is odd or < 2, or N >= 2^28.
  * ovl_geom_neighbors_device: fills dev_table, int32 [8][N] in eo order,
  *   table[d][eo(s)] = eo(neighbour of s), d = 0..3 for +x,+y,+z,+t and
  *   d = 4..7 for -x..-t, computed on the GPU by the same index arithmetic
@@ -540,7 +540,7 @@ int ovl_net_apply(const ovl_net* n, const ovl_gauge* u, const void* in, void* ou
 
 /* ovl_stencil_tune: mode 1 (default; OVL_TUNE=0 in the environment starts
  *   with 0) tunes each stencil configuration (precision, link format, extra
- *   epilogue vectors, batch size, parity mode, volume) at its first launch:
+ *   epilogue vectors, batch size, parity mode, extents) at its first launch:
  *   candidate shapes are timed with HIP events on a scratch output in two
  *   rounds of one warm-up and 3 timed launches (24 for batches below 8 MiB),
  *   and the first candidate within 2% of the fastest is kept.  Mode 0 uses
@@ -568,8 +568,8 @@ int ovl_net_apply(const ovl_net* n, const ovl_gauge* u, const void* in, void* ou
  *   full-lattice configuration (precision, link compression, number of
  *   extra epilogue vectors 0..3, batch size); all 0 when it has not been
  *   tuned yet.
- * ovl_stencil_set_shape: pins shape[5] for a configuration (all parity
- *   choices); OVL_E_ARG for shapes the kernels do not support.
+ * ovl_stencil_set_shape: pins shape[5] for a configuration on lattices of
+ *   g's extents (all parity choices); OVL_E_ARG for shapes the kernels do not support.
  */
 int ovl_stencil_tune(int mode);
 int ovl_stencil_shape(const ovl_geom* g, ovl_prec prec, int compress12, int nextra, int nrhs, int* shape);

@@ -126,7 +126,7 @@ int ovl_stencil_shape(const ovl_geom* g, ovl_prec prec, int compress12, int next
   return guard([&] {
     OVL_REQUIRE(g && shape, OVL_E_ARG, "null argument");
     for (int i = 0; i < 5; ++i) shape[i] = 0;
-    stencil_shape(prec, compress12 ? 12 : 18, nextra, nrhs, 2, g->geo.Nh, shape);
+    stencil_shape(prec, compress12 ? 12 : 18, nextra, nrhs, 2, g->geo, shape);
     return OVL_OK;
   });
 }
@@ -150,7 +150,7 @@ int ovl_stencil_set_shape(const ovl_geom* g, ovl_prec prec, int compress12, int 
       OVL_REQUIRE(!rin || bs * (nrhs / kr) <= 512, OVL_E_ARG, "rin shapes need bs * nrhs / kr <= 512");
     }
     for (int npar = 1; npar <= 2; ++npar)
-      force_shape(prec, compress12 ? 12 : 18, nextra, nrhs, npar, g->geo.Nh, shape);
+      force_shape(prec, compress12 ? 12 : 18, nextra, nrhs, npar, g->geo, shape);
     return OVL_OK;
   });
 }

@@ -26,11 +26,14 @@ void launch_shape(const StencilArgs& A, int prec, int recon, int nrhs, Shape sh,
 // is chosen once per process by timing every candidate with HIP events on a
 // scratch output; OVL_TUNE=0 keeps the static default.  Results are cached
 // in memory, keyed by precision, link format, extra vectors, batch size,
-// output parities and lattice volume.
+// output parities and lattice extents (a slab order needs as many z-planes).
 struct TuneKey {
-  int prec, recon, nv, nrhs, npar, nh;
+  int prec, recon, nv, nrhs, npar, lx, ly, lz, lt;
+  TuneKey(int prec, int recon, int nv, int nrhs, int npar, const Geo& g)
+      : prec(prec), recon(recon), nv(nv), nrhs(nrhs), npar(npar), lx(g.Lx), ly(g.Ly), lz(g.Lz), lt(g.Lt) {}
   bool operator<(const TuneKey& o) const {
-    return std::tie(prec, recon, nv, nrhs, npar, nh) < std::tie(o.prec, o.recon, o.nv, o.nrhs, o.npar, o.nh);
+    return std::tie(prec, recon, nv, nrhs, npar, lx, ly, lz, lt) <
+           std::tie(o.prec, o.recon, o.nv, o.nrhs, o.npar, o.lx, o.ly, o.lz, o.lt);
   }
 };
 
@@ -84,7 +87,7 @@ Shape default_shape(int prec, int nrhs) {
 }
 
 Shape pick_shape(const StencilArgs& A, int prec, int recon, int nrhs, hipStream_t s) {
-  const TuneKey key{prec, recon, A.nv, nrhs, A.npar, A.g.Nh};
+  const TuneKey key(prec, recon, A.nv, nrhs, A.npar, A.g);
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tuned.find(key);
@@ -230,9 +233,9 @@ void set_tune_mode(int mode) {
   g_tuned.clear();
 }
 
-int stencil_shape(int prec, int recon, int nv, int nrhs, int npar, int nh, int* shape5) {
+int stencil_shape(int prec, int recon, int nv, int nrhs, int npar, const Geo& g, int* shape5) {
   std::lock_guard<std::mutex> lk(g_tune_mu);
-  auto it = g_tuned.find(TuneKey{prec, recon, nv, nrhs, npar, nh});
+  auto it = g_tuned.find(TuneKey(prec, recon, nv, nrhs, npar, g));
   if (it == g_tuned.end()) return 0;
   const Shape& sh = it->second;
   shape5[0] = sh.kr;
@@ -243,9 +246,9 @@ int stencil_shape(int prec, int recon, int nv, int nrhs, int npar, int nh, int* 
   return 1;
 }
 
-void force_shape(int prec, int recon, int nv, int nrhs, int npar, int nh, const int* shape5) {
+void force_shape(int prec, int recon, int nv, int nrhs, int npar, const Geo& g, const int* shape5) {
   std::lock_guard<std::mutex> lk(g_tune_mu);
-  g_tuned[TuneKey{prec, recon, nv, nrhs, npar, nh}] = Shape{shape5[0], shape5[1], shape5[2], shape5[3], shape5[4]};
+  g_tuned[TuneKey(prec, recon, nv, nrhs, npar, g)] = Shape{shape5[0], shape5[1], shape5[2], shape5[3], shape5[4]};
 }
 
 }  // namespace ovl

@@ -38,9 +38,9 @@ void launch_stencil(const StencilArgs& A, int prec, int recon, int nrhs, hipStre
 // Changing the mode clears the tuned table.
 void set_tune_mode(int mode);
 // Tuned shape of a configuration, if any: returns 1 and fills kr, bs, pipe.
-int stencil_shape(int prec, int recon, int nv, int nrhs, int npar, int nh, int* shape5);
+int stencil_shape(int prec, int recon, int nv, int nrhs, int npar, const Geo& g, int* shape5);
 // Pins the shape of a configuration (tests, measurements).
-void force_shape(int prec, int recon, int nv, int nrhs, int npar, int nh, const int* shape5);
+void force_shape(int prec, int recon, int nv, int nrhs, int npar, const Geo& g, const int* shape5);
 
 // Representation of the links that operators at spinor precision prec use.
 const void* gauge_links(const ovl_gauge* u, int prec, int* recon);

@@ -112,3 +112,18 @@ def test_rational_coefficients_match_the_oracle(n, lo, hi):
         ovl.Rational(lo, hi, 0)
     with pytest.raises(ovl.OvlError):
         ovl.Rational(hi, lo, 4)
+
+
+def test_a_pinned_shape_holds_for_its_extents_only():
+    """A slab order pinned on one lattice is not taken on another of the same
+    volume, which may have fewer z-planes than the slab."""
+    from paper_1106_4964_amd import ovl
+
+    a, b = ovl.Geometry((4, 4, 8, 4)), ovl.Geometry((8, 4, 2, 8))
+    assert a.N == b.N
+    try:
+        ovl.stencil_set_shape(a, ovl.OVL_F64, 0, 1, 1, (1, 256, 0, 0, 8))
+        assert ovl.stencil_shape(ovl.Geometry((4, 4, 8, 4)), ovl.OVL_F64, 0, 1, 1) == (1, 256, 0, 0, 8)
+        assert ovl.stencil_shape(b, ovl.OVL_F64, 0, 1, 1) == (0, 0, 0, 0, 0)
+    finally:
+        ovl.ovl_stencil_tune(1)

@@ -290,3 +290,21 @@ def test_split_directions_kernel(prec, dims):
                     res.append(gu.unpack(g, out, prec, nrhs))
                 # ten stages, each within a rounding of its output of the other kernel's
                 assert gu.rel_err(res[0], res[1]) < 20 * u, (c12, nrhs, kr, tm)
+
+
+def test_lattices_of_equal_volume_have_their_own_shapes():
+    """D_w on a lattice with two z-planes after a slab order of eight was pinned
+    on one of the same volume."""
+    dims = (8, 4, 2, 8)
+    lat = Lattice(dims)
+    U = si.gauge_field(dims, 0.3, 6)
+    psi = si.gaussian_spinor(dims, 8)
+    try:
+        ovl.stencil_set_shape(ovl.Geometry((4, 4, 8, 4)), ovl.OVL_F64, 0, 0, 1, (1, 256, 0, 0, 8))
+        g = ovl.Geometry(dims)
+        out = gu.empty_field(g, ovl.OVL_F64)
+        ovl.ovl_dslash(out, gu.pack(g, psi, ovl.OVL_F64), gu.make_gauge(g, U), 0.1, 2, ovl.OVL_F64, 1, None)
+        got = gu.unpack(g, out, ovl.OVL_F64)
+    finally:
+        ovl.ovl_stencil_tune(1)
+    assert gu.max_rel_err(got, dirac.wilson_dslash(lat, U, psi, 0.1)) < 1e-13
