@@ -127,3 +127,15 @@ def test_a_pinned_shape_holds_for_its_extents_only():
         assert ovl.stencil_shape(b, ovl.OVL_F64, 0, 1, 1) == (0, 0, 0, 0, 0)
     finally:
         ovl.ovl_stencil_tune(1)
+
+
+@pytest.mark.parametrize("first", [True, False])
+def test_a_pinned_shape_does_not_outlive_its_test(first):
+    """The first of the two pins a shape and leaves it, the second finds none."""
+    from paper_1106_4964_amd import ovl
+
+    g = ovl.Geometry((4, 4, 4, 6))
+    shape = (1, 128, 0, 0, 1)
+    if first:
+        ovl.stencil_set_shape(g, ovl.OVL_F64, 0, 2, 3, shape)
+    assert ovl.stencil_shape(g, ovl.OVL_F64, 0, 2, 3) == (shape if first else (0, 0, 0, 0, 0))
