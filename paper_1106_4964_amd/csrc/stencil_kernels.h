@@ -482,23 +482,24 @@ __device__ inline void raw_project(const SpinorRaw<P>& sr, Cx<typename Prec<P>::
   }
 }
 
-// ph * (a - m f) for the phase ph coded as in proj1; m = 1 or 2.
+// ph * (a - f) for the phase ph coded as in proj1.
 template <int PH, typename T>
-__device__ inline Cx<T> phase_diff(Cx<T> a, T m, Cx<T> f) {
-  if constexpr (PH == 0) return {ffma(-m, f.re, a.re), ffma(-m, f.im, a.im)};
-  else if constexpr (PH == 1) return {ffma(m, f.re, -a.re), ffma(m, f.im, -a.im)};
-  else if constexpr (PH == 2) return {ffma(m, f.im, -a.im), ffma(-m, f.re, a.re)};
-  else return {ffma(-m, f.im, a.im), ffma(m, f.re, -a.re)};
+__device__ inline Cx<T> phase_diff(Cx<T> a, Cx<T> f) {
+  if constexpr (PH == 0) return {a.re - f.re, a.im - f.im};
+  else if constexpr (PH == 1) return {f.re - a.re, f.im - a.im};
+  else if constexpr (PH == 2) return {f.im - a.im, a.re - f.re};
+  else return {a.im - f.im, f.re - a.re};
 }
 
 // Both hops of direction MU for KR vectors, val[k] = the 12 components of
 // U_mu(x)(1 - gamma_mu) in(x+mu) + U_mu(x-mu)^dag (1 + gamma_mu) in(x-mu).
 // With f and g the two transported half spinors, the upper spins are f + g and
-// the lower spins a phase times g - f: 24 instructions where adding the two
-// hops one after the other takes 48.  At 16-bit storage g's colour products
-// are accumulated onto f and g - f = (f + g) - 2 f, 12 instructions; in FP32
-// that raised the error of H_w against 64 bits from 5.96e-8 to 6.21e-8, so
-// there (and in FP64) both are rounded once from f and g.
+// the lower spins a phase times g - f, each rounded once: 24 instructions where
+// adding the two hops one after the other takes 48.  (g's colour products
+// accumulated onto f, and g - f = (f + g) - 2 f, would save 12 more, but round
+// once more: H_w in FP32 6.21e-8 from the 64-bit result against 5.96e-8, and at
+// F16 storage 4.66 of 10^4 stored reals other than the exact ones' rounding,
+// where this has 4.23 and the hops added one after the other 4.34.)
 template <int P, int R, int MU, int KR>
 __device__ inline void split_hop(const StencilArgs& A, const char* in, int p, int h, int x, int y, int z, int t,
                                  Cx<typename Prec<P>::real> (*val)[12]) {
@@ -543,33 +544,15 @@ __device__ inline void split_hop(const StencilArgs& A, const char* in, int p, in
   constexpr int s0 = MU < 2 ? 1 : 0, s1 = MU < 2 ? 0 : 1;
 #pragma unroll
   for (int k = 0; k < KR; ++k) {
-    Cx<real> hs[2][3];
+    Cx<real> hs[2][3], g[2][3];
     raw_project<P, MU, +1>(sb[k], hs);
-    if constexpr (P == OVL_F16 || P == OVL_BF16) {
+    colour_mul<true>(u, hs, g);
 #pragma unroll
-      for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-          real re = f[k][s][a].re, im = f[k][s][a].im;
-#pragma unroll
-          for (int c = 0; c < 3; ++c) cmac<true>(re, im, u[c][a], hs[s][c]);
-          val[k][3 * s + a] = {re, im};
-        }
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        val[k][6 + c] = phase_diff<l0>(val[k][3 * s0 + c], real(2), f[k][s0][c]);
-        val[k][9 + c] = phase_diff<l1>(val[k][3 * s1 + c], real(2), f[k][s1][c]);
-      }
-    } else {
-      Cx<real> b[2][3];
-      colour_mul<true>(u, hs, b);
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        val[k][c] = f[k][0][c] + b[0][c];
-        val[k][3 + c] = f[k][1][c] + b[1][c];
-        val[k][6 + c] = phase_diff<l0>(b[s0][c], real(1), f[k][s0][c]);
-        val[k][9 + c] = phase_diff<l1>(b[s1][c], real(1), f[k][s1][c]);
-      }
+    for (int c = 0; c < 3; ++c) {
+      val[k][c] = f[k][0][c] + g[0][c];
+      val[k][3 + c] = f[k][1][c] + g[1][c];
+      val[k][6 + c] = phase_diff<l0>(g[s0][c], f[k][s0][c]);
+      val[k][9 + c] = phase_diff<l1>(g[s1][c], f[k][s1][c]);
     }
   }
 }

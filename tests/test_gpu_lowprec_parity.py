@@ -116,3 +116,83 @@ def test_overlap_12rhs_projected_8888(c8, prec, dagger):
     print("8^4 D(m)%s prec %d, 12 rhs, l = 24, n = 100: element-wise errors %s"
           % ("^dag" if dagger else "", prec, " ".join("%.2e" % e for e in errs)))
     assert max(errs) < BOUND_8888[prec]
+
+
+def _f16(a):
+    """The nearest F16 numbers, as complex128 and as the float64 reals."""
+    h = np.ascontiguousarray(a).view(np.float64).astype(np.float16).astype(np.float64)
+    return h.view(np.complex128), h
+
+
+def _hw_hops_in_turn(lat, U, psi, rho):
+    """H_w of F16 numbers in FP32 FMAs, each hop added to the sum as it is formed
+    (forward, backward, direction by direction), then rounded to F16.  Arrays are
+    float32 (re, im) pairs; the float64 product of two float32 is exact."""
+    f4 = np.float32
+
+    def fma(x, y, z):
+        return (x.astype(np.float64) * y + z).astype(f4)
+
+    def parts(v):
+        return np.stack([v.real, v.imag], -1).astype(f4)
+
+    p, u = parts(psi.reshape(lat.shape + (4, 3))), parts(U.reshape(lat.shape + (4, 3, 3)))
+    acc = np.zeros_like(p)
+    half = f4(-0.5)
+    turn = {1: lambda v: v, -1: lambda v: -v, 1j: lambda v: np.stack([-v[..., 1], v[..., 0]], -1),
+            -1j: lambda v: np.stack([v[..., 1], -v[..., 0]], -1)}
+    for mu in range(4):
+        gam = dirac.GAMMA[mu]
+        for s in (-1, 1):  # forward (1 - gamma), backward (1 + gamma)
+            n = np.roll(p, s, axis=3 - mu)
+            link = u[..., mu, :, :, :] if s < 0 else np.roll(u[..., mu, :, :, :], 1, axis=3 - mu)
+            w = []
+            for k in range(2):
+                j = int(np.argmax(np.abs(gam[k])))
+                h = n[..., k, :, :] + turn[complex(s * gam[k, j])](n[..., j, :, :])
+                rows = []
+                for a in range(3):
+                    re = im = np.zeros(lat.shape, f4)
+                    for b in range(3):
+                        v = link[..., a, b, :] if s < 0 else link[..., b, a, :] * np.array([1, -1], f4)
+                        re, im = fma(v[..., 0], h[..., b, 0], re), fma(v[..., 0], h[..., b, 1], im)
+                        re, im = fma(-v[..., 1], h[..., b, 1], re), fma(v[..., 1], h[..., b, 0], im)
+                    rows.append(np.stack([re, im], -1))
+                w.append(np.stack(rows, -2))
+            for k in range(4):
+                if k < 2:
+                    add = w[k]
+                else:  # gamma chi = s chi for chi = (1 + s gamma) psi
+                    j = int(np.argmax(np.abs(gam[k, :2])))
+                    add = turn[complex(s * gam[k, j])](w[j])
+                acc[..., k, :, :] = fma(add, half, acc[..., k, :, :])
+    acc = fma(p, f4(4.0 - rho), acc)
+    acc[..., 2:, :, :] *= f4(-1)
+    return acc.astype(np.float16).astype(np.float64).reshape(-1)
+
+
+def test_f16_stencil_rounds_no_more_than_hops_added_in_turn():
+    """H_w at F16 storage with every input an F16 number: the stored reals that
+    are not the rounding of the exact value (the FP64 stencil on the same
+    numbers) count the FP32 arithmetic's roundings, which the storage rounding
+    hides from the usual error.  No more than the plainest FP32 form leaves on
+    the same numbers, within three standard deviations of its count."""
+    dims = (8, 8, 12, 16)
+    lat = Lattice(dims)
+    g = ovl.Geometry(dims)
+    wrong = plain = 0
+    for seed in range(6):
+        U = _f16(si.gauge_field(dims, 0.25, 30 + seed))[0]
+        gauge = gu.make_gauge(g, U, [(F16, 0)])
+        psi = np.stack([_f16(si.gaussian_spinor(dims, 100 * seed + r))[0] for r in range(R)])
+        got = {}
+        for prec in (F16, F64):
+            out = gu.empty_field(g, prec, R)
+            ovl.ovl_hw_apply(out, gu.pack(g, psi, prec, R), gauge, RHO, prec, R, None)
+            got[prec] = np.ascontiguousarray(gu.unpack(g, out, prec, R))
+        want = _f16(got[F64])[1].reshape(R, -1)
+        wrong += int(np.count_nonzero(got[F16].view(np.float64).reshape(R, -1) != want))
+        for r in range(R):
+            plain += int(np.count_nonzero(_hw_hops_in_turn(lat, U, psi[r], RHO) != want[r]))
+    print("F16 H_w: reals off the exact value's rounding %d, hops in turn %d of %d" % (wrong, plain, 6 * R * 24 * g.N))
+    assert wrong <= plain + 3 * np.sqrt(plain)
