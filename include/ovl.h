@@ -563,7 +563,7 @@ int ovl_net_apply(const ovl_net* n, const ovl_gauge* u, const void* in, void* ou
  *   of tm = 4 or 8 z-planes at t, then the same slab at t + 1, ..., so a
  *   site's t-neighbours are read a slab apart instead of a whole 3-d slice;
  *   the last slab may be thinner).  shape[4] = tm: 0 h order, 1 t-major,
- *   2..Lz slab thickness.
+ *   2..Lz slab thickness.  Every shape gives the same result to the last bit.
  * ovl_stencil_shape: shape[5] = {kr, bs, pipe, rin, tm} tuned for a
  *   full-lattice configuration (precision, link compression, number of
  *   extra epilogue vectors 0..3, batch size); all 0 when it has not been

@@ -55,11 +55,12 @@ bool tuning_enabled() {
 // The shapes that win somewhere (all shapes timed on 30 lattices, precisions
 // and batch sizes from 4^4 to 32^3x64): split directions (256 threads)
 // nearly everywhere, by 2-45%; the groups of vectors side by side in one
-// workgroup, which share their links through L1, for FP32 batches (12 rhs at
-// 24^3x64: 935 against 960 us, at 16^3x32: 125 against 134 us).  One
+// workgroup, which share their links through L1, for FP32 and FP64 batches
+// (12 rhs at 24^3x64: FP32 802 against 840 us without and 1216 against 1246
+// with three extra vectors, FP64 2062 against 1989 and 2841 against 3001).  One
 // direction after the other with a group per block (128 threads) loses
-// everywhere (F16, 12 rhs at 24^3x64: 520 against 469 us; 4^4 FP64: 6.3
-// against 4.2 us) and is only run when pinned.
+// everywhere (F16, 12 rhs at 24^3x64: 419 against 390 us; 4^4 FP64: 6.3
+// against 4.2 us) and is only run when pinned.  All of them give the same bits.
 std::vector<Shape> candidates(int prec, int nrhs, int Lz, size_t batch_bytes) {
   std::vector<Shape> c;
   const int kmax = prec == OVL_F64 ? 2 : 4;

@@ -9,7 +9,9 @@
 // lower two spin components being fixed multiples of the upper two (chiral
 // basis).  stencil_split_kernel shares a site between four threads, one per
 // direction; stencil_kernel does a site's 8 hops in one thread.  Both treat
-// KR right-hand sides per thread.  The epilogue forms
+// KR right-hand sides per thread and add the same terms in the same order
+// (the two hops of a direction, then the directions by mu), so that a result
+// does not depend on the shape that the tuner took.  The epilogue forms
 // G(a*in + b*hop) + sum_j c_j G_j(v_j) at the output site, which covers
 // D_w(m), H_w = gamma5 D_w(-rho), and the Clenshaw update of the polynomial
 // sign function (Sec. V) in one pass.
@@ -81,26 +83,6 @@ __device__ inline void addph(Cx<T>& a, Cx<T> w, T s) {
   } else {  // - i w = (w.im, -w.re)
     a.re = ffma(s, w.im, a.re);
     a.im = ffma(-s, w.re, a.im);
-  }
-}
-
-// Adds the reconstructed direction term: upper spins += bu * w, lower spins
-// += bl * (phase) w.  bu = b and bl = +-b carry the hopping weight of the
-// epilogue and, for gamma5 outputs, the sign of the lower spins, so neither
-// costs an instruction of its own.
-template <int MU, int SGN, typename T>
-__device__ inline void accumulate(Cx<T>* acc, const Cx<T> (*w)[3], T bu, T bl) {
-  // phase code and source spin (0 or 1) of lower spins 2 and 3
-  constexpr bool F = SGN < 0;
-  constexpr int l0 = MU == 0 ? (F ? 3 : 2) : MU == 1 ? (F ? 1 : 0) : MU == 2 ? (F ? 3 : 2) : (F ? 1 : 0);
-  constexpr int l1 = MU == 0 ? (F ? 3 : 2) : MU == 1 ? (F ? 0 : 1) : MU == 2 ? (F ? 2 : 3) : (F ? 1 : 0);
-  constexpr int s0 = MU < 2 ? 1 : 0, s1 = MU < 2 ? 0 : 1;
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    addph<0>(acc[c], w[0][c], bu);
-    addph<0>(acc[3 + c], w[1][c], bu);
-    addph<l0>(acc[6 + c], w[s0][c], bl);
-    addph<l1>(acc[9 + c], w[s1][c], bl);
   }
 }
 
@@ -221,57 +203,8 @@ __device__ inline void opaque_link(Cx<typename Prec<P>::real> (*u)[3]) {
   }
 }
 
-template <int P, int R, int MU, int KR>
-__device__ inline void hop_dir(const StencilArgs& A, const char* in, int p, int h, const int* nb,
-                               Cx<typename Prec<P>::real> (*acc)[12], typename Prec<P>::real bu,
-                               typename Prec<P>::real bl) {
-  using real = typename Prec<P>::real;
-  const int q = 1 - p;
-  Cx<real> hs[2][3], w[2][3], u[3][3];
-  // forward: U_mu(x) (1 - gamma_mu) in(x + mu), the link shared by the KR vectors
-  LinkIO<P, R>::load(A.links, MU, p, h, A.g.Nh, u);
-  opaque_link<P>(u);
-#pragma unroll
-  for (int k = 0; k < KR; ++k) {
-    if constexpr (P == OVL_F16) {
-      SpinorRaw<P> r;
-      spinor_load_raw<P>(in + k * A.vstride, q, nb[MU], A.g.Nh, r);
-      uint32_t sw[12];
-#pragma unroll
-      for (int c = 0; c < 12; ++c) sw[c] = raw_word(r, c);
-      project_f16<MU, -1>(sw, hs);
-    } else {
-      Cx<real> s[12];
-      SpinorIO<P>::load(in + k * A.vstride, q, nb[MU], A.g.Nh, s);
-      project<MU, -1>(s, hs);
-    }
-    colour_mul<false>(u, hs, w);
-    accumulate<MU, -1>(acc[k], w, bu, bl);
-  }
-  // backward: U_mu(x - mu)^dag (1 + gamma_mu) in(x - mu)
-  LinkIO<P, R>::load(A.links, MU, q, nb[MU + 4], A.g.Nh, u);
-  opaque_link<P>(u);
-#pragma unroll
-  for (int k = 0; k < KR; ++k) {
-    if constexpr (P == OVL_F16) {
-      SpinorRaw<P> r;
-      spinor_load_raw<P>(in + k * A.vstride, q, nb[MU + 4], A.g.Nh, r);
-      uint32_t sw[12];
-#pragma unroll
-      for (int c = 0; c < 12; ++c) sw[c] = raw_word(r, c);
-      project_f16<MU, +1>(sw, hs);
-    } else {
-      Cx<real> s[12];
-      SpinorIO<P>::load(in + k * A.vstride, q, nb[MU + 4], A.g.Nh, s);
-      project<MU, +1>(s, hs);
-    }
-    colour_mul<true>(u, hs, w);
-    accumulate<MU, +1>(acc[k], w, bu, bl);
-  }
-}
-
-// Hopping weights of the accumulation: b on the upper spins, and on the
-// lower spins b, or -b when the output takes gamma5.
+// Hopping weights of the epilogue: b on the upper spins, and on the lower
+// spins b, or -b when the output takes gamma5.
 template <typename T>
 __device__ inline void hop_weights(const StencilArgs& A, T& bu, T& bl) {
   bu = static_cast<T>(A.b);
@@ -279,12 +212,15 @@ __device__ inline void hop_weights(const StencilArgs& A, T& bu, T& bl) {
 }
 
 // Epilogue at the output site: G(a*in + b*hop) + sum_j c_j G_j(v_j), G = 1
-// or gamma5, then the store.  acc already holds b*hop with G's sign on the
-// lower spins.
+// or gamma5, then the store; acc holds hop.
 template <int P, int NV>
 __device__ inline void epilogue(const StencilArgs& A, size_t off, int p, int h, Cx<typename Prec<P>::real>* acc) {
   using real = typename Prec<P>::real;
   const real au = static_cast<real>(A.a), al = A.g5 ? -au : au;
+  real bu, bl;
+  hop_weights(A, bu, bl);
+#pragma unroll
+  for (int c = 0; c < 12; ++c) acc[c] = (c >= 6 ? bl : bu) * acc[c];
   if constexpr (P == OVL_F16) {
     SpinorRaw<P> r;
     spinor_load_raw<P>(static_cast<const char*>(A.in) + off, p, h, A.g.Nh, r);
@@ -371,42 +307,6 @@ __device__ inline bool stencil_site(const StencilArgs& A, int& p, int& h) {
                    p, h);
 }
 
-// One thread: one output site and KR consecutive vectors of the batch, so
-// each link is loaded and rebuilt once per KR right-hand sides.  With
-// RIN = false the group of KR vectors is blockIdx.y (one pass over the
-// lattice per group); with RIN = true it is threadIdx.y, so all groups of a
-// site tile run in the same workgroup and share its links and neighbour
-// spinors through L1/L2 (one pass over the lattice for the whole batch).
-template <int P, int R, int NV, int KR, bool RIN>
-__global__ __launch_bounds__(RIN ? 512 : 256) void stencil_kernel(StencilArgs A) {
-  using real = typename Prec<P>::real;
-  const Geo& g = A.g;
-  int p, h;
-  if (!stencil_site(A, p, h)) return;
-  const int group = RIN ? threadIdx.y : blockIdx.y;
-  const size_t voff = static_cast<size_t>(group) * KR * A.vstride;
-  const char* in = static_cast<const char*>(A.in) + voff;
-
-  int x, y, z, t, nb[8];
-  site_coords(g, p, h, x, y, z, t);
-  site_neighbors(g, h, x, y, z, t, nb);
-
-  Cx<real> acc[KR][12];
-#pragma unroll
-  for (int k = 0; k < KR; ++k)
-#pragma unroll
-    for (int c = 0; c < 12; ++c) acc[k][c] = {real(0), real(0)};
-  real bu, bl;
-  hop_weights(A, bu, bl);
-  hop_dir<P, R, 0, KR>(A, in, p, h, nb, acc, bu, bl);
-  hop_dir<P, R, 1, KR>(A, in, p, h, nb, acc, bu, bl);
-  hop_dir<P, R, 2, KR>(A, in, p, h, nb, acc, bu, bl);
-  hop_dir<P, R, 3, KR>(A, in, p, h, nb, acc, bu, bl);
-
-#pragma unroll
-  for (int k = 0; k < KR; ++k) epilogue<P, NV>(A, voff + k * A.vstride, p, h, acc[k]);
-}
-
 // ------------------------------------------------------- split directions
 // One workgroup of four waves per tile of 64 sites: wave w computes the two
 // hops of direction mu = w for KR vectors of every site, and the four partial
@@ -422,10 +322,10 @@ __global__ __launch_bounds__(RIN ? 512 : 256) void stencil_kernel(StencilArgs A)
 //  - a quarter of the sites in flight per XCD, so that neighbours and links
 //    are found in its L2: 24^3x64 F16, 12 rhs, no extra vectors: 1.10 ->
 //    0.53 million KiB FETCH_SIZE a launch.
-//  - the two hops of a direction share the addition (split_hop).
+//  - the two hops of a direction share the addition (hops).
 // 24^3x64 (H_w / Clenshaw step with three extra vectors, us): F16 12 rhs
 // 435 / 635 -> 395 / 600, FP32-12 1 rhs 85 / 115 -> 76 / 110, FP64 1 rhs
-// 228 / 304 -> 214 / 299, FP64 12 rhs 1988 (start) -> 1800.
+// 228 / 304 -> 214 / 299, FP64 12 rhs 2132 / 2794 -> 1989 / 3001.
 // What bounds it there: with three extra vectors HBM (3.1 GB at 5.2 TB/s);
 // without, the reads between L1 and L2 (34 million 128-byte requests in 0.4 ms
 // for F16, 11 TB/s; 93 million in 0.88 ms for FP32, 13 TB/s) and the FP32
@@ -491,18 +391,30 @@ __device__ inline Cx<T> phase_diff(Cx<T> a, Cx<T> f) {
   else return {a.im - f.im, f.re - a.re};
 }
 
-// Both hops of direction MU for KR vectors, val[k] = the 12 components of
-// U_mu(x)(1 - gamma_mu) in(x+mu) + U_mu(x-mu)^dag (1 + gamma_mu) in(x-mu).
-// With f and g the two transported half spinors, the upper spins are f + g and
-// the lower spins a phase times g - f, each rounded once: 24 instructions where
-// adding the two hops one after the other takes 48.  (g's colour products
-// accumulated onto f, and g - f = (f + g) - 2 f, would save 12 more, but round
-// once more: H_w in FP32 6.21e-8 from the 64-bit result against 5.96e-8, and at
-// F16 storage 4.66 of 10^4 stored reals other than the exact ones' rounding,
-// where this has 4.23 and the hops added one after the other 4.34.)
-template <int P, int R, int MU, int KR>
-__device__ inline void split_hop(const StencilArgs& A, const char* in, int p, int h, int x, int y, int z, int t,
-                                 Cx<typename Prec<P>::real> (*val)[12]) {
+// Ends the arithmetic of these numbers here: the compiler otherwise puts off
+// a direction's products until the next ones' operands are loaded, and all
+// eight hops' operands then want registers (256 VGPRs and scratch).
+template <typename T>
+__device__ inline void keep(T& x) {
+  using E = std::remove_all_extents_t<T>;
+  E* e = reinterpret_cast<E*>(&x);
+#pragma unroll
+  for (size_t i = 0; i < sizeof(T) / sizeof(E); ++i) asm volatile("" : "+v"(e[i].re), "+v"(e[i].im));
+}
+
+// Both hops of direction MU for KR vectors,
+// U_mu(x)(1 - gamma_mu) in(x+mu) + U_mu(x-mu)^dag (1 + gamma_mu) in(x-mu),
+// into val[k] (SPLIT, or MU = 0) or added to it.  With f and g the two
+// transported half spinors, the upper spins are f + g and the lower spins a
+// phase times g - f, each rounded once: 24 instructions where adding the two
+// hops one after the other takes 48.  (g's colour products accumulated onto f,
+// and g - f = (f + g) - 2 f, would save 12 more, but round once more: H_w in
+// FP32 6.21e-8 from the 64-bit result against 5.96e-8, and at F16 storage 4.66
+// of 10^4 stored reals other than the exact ones' rounding, where this has 4.23
+// and the hops added one after the other 4.34.)
+template <int P, int R, int MU, int KR, bool SPLIT>
+__device__ inline void hops(const StencilArgs& A, const char* in, int p, int h, int x, int y, int z, int t,
+                            Cx<typename Prec<P>::real> (*val)[12]) {
   using real = typename Prec<P>::real;
   using LF = LinkFmt<P, R>;
   const int Nh = A.g.Nh, q = 1 - p;
@@ -515,15 +427,19 @@ __device__ inline void split_hop(const StencilArgs& A, const char* in, int p, in
   SpinorRaw<P> sf[KR], sb[KR];
   LinkRaw<P, R> lf, lb;
   raw_link_at<P, R>(lk + p * lpar, static_cast<uint32_t>(h), Nh, lf);
+  auto forward = [&](int k) { raw_spinor_at<P>(src + k * A.vstride, hf * 16u, Nh, sf[k]); };
+  auto backward = [&](int k) { raw_spinor_at<P>(src + k * A.vstride, hb * 16u, Nh, sb[k]); };
+  if constexpr (SPLIT)
 #pragma unroll
-  for (int k = 0; k < KR; ++k) raw_spinor_at<P>(src + k * A.vstride, hf * 16u, Nh, sf[k]);
+    for (int k = 0; k < KR; ++k) forward(k);
   auto load_back = [&] {
     raw_link_at<P, R>(lk + q * lpar, hb, Nh, lb);
+    if constexpr (SPLIT)
 #pragma unroll
-    for (int k = 0; k < KR; ++k) raw_spinor_at<P>(src + k * A.vstride, hb * 16u, Nh, sb[k]);
+      for (int k = 0; k < KR; ++k) backward(k);
   };
   // both hops' operands in flight at once while they fit the registers
-  constexpr bool ahead = 2 * (sizeof(SpinorRaw<P>) * KR + sizeof(LinkRaw<P, R>)) <= 680;
+  constexpr bool ahead = SPLIT && 2 * (sizeof(SpinorRaw<P>) * KR + sizeof(LinkRaw<P, R>)) <= 680;
   if constexpr (ahead) {
     load_back();
     __builtin_amdgcn_sched_barrier(0);
@@ -533,10 +449,12 @@ __device__ inline void split_hop(const StencilArgs& A, const char* in, int p, in
 #pragma unroll
   for (int k = 0; k < KR; ++k) {
     Cx<real> hs[2][3];
+    if constexpr (!SPLIT) forward(k);
     raw_project<P, MU, -1>(sf[k], hs);
     colour_mul<false>(u, hs, f[k]);
   }
   if constexpr (ahead) __builtin_amdgcn_sched_barrier(0);
+  if constexpr (!SPLIT) keep(f);
   if constexpr (!ahead) load_back();
   raw_link_unpack<P, R>(lb, u);
   constexpr int l0 = MU == 0 ? 2 : MU == 1 ? 0 : MU == 2 ? 2 : 0;
@@ -545,16 +463,48 @@ __device__ inline void split_hop(const StencilArgs& A, const char* in, int p, in
 #pragma unroll
   for (int k = 0; k < KR; ++k) {
     Cx<real> hs[2][3], g[2][3];
+    if constexpr (!SPLIT) backward(k);
     raw_project<P, MU, +1>(sb[k], hs);
     colour_mul<true>(u, hs, g);
+    auto put = [&](int c, Cx<real> v) { val[k][c] = SPLIT || MU == 0 ? v : val[k][c] + v; };
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      val[k][c] = f[k][0][c] + g[0][c];
-      val[k][3 + c] = f[k][1][c] + g[1][c];
-      val[k][6 + c] = phase_diff<l0>(g[s0][c], f[k][s0][c]);
-      val[k][9 + c] = phase_diff<l1>(g[s1][c], f[k][s1][c]);
+      put(c, f[k][0][c] + g[0][c]);
+      put(3 + c, f[k][1][c] + g[1][c]);
+      put(6 + c, phase_diff<l0>(g[s0][c], f[k][s0][c]));
+      put(9 + c, phase_diff<l1>(g[s1][c], f[k][s1][c]));
     }
   }
+  if constexpr (!SPLIT) keep(*reinterpret_cast<Cx<real>(*)[KR][12]>(val));
+}
+
+// One thread: one output site and KR consecutive vectors of the batch, so
+// each link is loaded and rebuilt once per KR right-hand sides.  With
+// RIN = false the group of KR vectors is blockIdx.y (one pass over the
+// lattice per group); with RIN = true it is threadIdx.y, so all groups of a
+// site tile run in the same workgroup and share its links and neighbour
+// spinors through L1/L2 (one pass over the lattice for the whole batch).
+template <int P, int R, int NV, int KR, bool RIN>
+__global__ __launch_bounds__(RIN ? 512 : 256) void stencil_kernel(StencilArgs A) {
+  using real = typename Prec<P>::real;
+  const Geo& g = A.g;
+  int p, h;
+  if (!stencil_site(A, p, h)) return;
+  const int group = RIN ? threadIdx.y : blockIdx.y;
+  const size_t voff = static_cast<size_t>(group) * KR * A.vstride;
+  const char* in = static_cast<const char*>(A.in) + voff;
+
+  int x, y, z, t;
+  site_coords(g, p, h, x, y, z, t);
+
+  Cx<real> acc[KR][12];
+  hops<P, R, 0, KR, false>(A, in, p, h, x, y, z, t, acc);
+  hops<P, R, 1, KR, false>(A, in, p, h, x, y, z, t, acc);
+  hops<P, R, 2, KR, false>(A, in, p, h, x, y, z, t, acc);
+  hops<P, R, 3, KR, false>(A, in, p, h, x, y, z, t, acc);
+
+#pragma unroll
+  for (int k = 0; k < KR; ++k) epilogue<P, NV>(A, voff + k * A.vstride, p, h, acc[k]);
 }
 
 // Epilogue of one 16-byte output block u (components u*cpb ...): a = the sum
@@ -610,10 +560,10 @@ __global__ __launch_bounds__(256) void stencil_split_kernel(StencilArgs A) {
   site_coords(g, p, h, x, y, z, t);
   Cx<real> val[KR][12];
   switch (w) {
-    case 0: split_hop<P, R, 0, KR>(A, in, p, h, x, y, z, t, val); break;
-    case 1: split_hop<P, R, 1, KR>(A, in, p, h, x, y, z, t, val); break;
-    case 2: split_hop<P, R, 2, KR>(A, in, p, h, x, y, z, t, val); break;
-    default: split_hop<P, R, 3, KR>(A, in, p, h, x, y, z, t, val); break;
+    case 0: hops<P, R, 0, KR, true>(A, in, p, h, x, y, z, t, val); break;
+    case 1: hops<P, R, 1, KR, true>(A, in, p, h, x, y, z, t, val); break;
+    case 2: hops<P, R, 2, KR, true>(A, in, p, h, x, y, z, t, val); break;
+    default: hops<P, R, 3, KR, true>(A, in, p, h, x, y, z, t, val); break;
   }
 
   // Output blocks of this wave: block 4 i + (w + k) % 4 of vector k.  The
@@ -664,7 +614,7 @@ __global__ __launch_bounds__(256) void stencil_split_kernel(StencilArgs A) {
             __builtin_memcpy(reinterpret_cast<char*>(b[s]) + 16 * c, &v, 16);
           }
 #pragma unroll
-        for (int j = 0; j < cpb; ++j) a[j] = (b[0][j] + b[1][j]) + (b[2][j] + b[3][j]);
+        for (int j = 0; j < cpb; ++j) a[j] = ((b[0][j] + b[1][j]) + b[2][j]) + b[3][j];
         split_block<P, NV>(A, block_off(k, u) + hoff, u, rin[k][i], rv[k][i], a);
       }
     }
