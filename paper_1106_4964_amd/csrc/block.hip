@@ -11,13 +11,12 @@
 // (parity p, complex index c) of N/2 sites, so a complex number is addressed
 // the same way whatever the storage precision of the batch.
 //
-// All three are contractions in FP64 and run on the FP64 matrix cores
-// (v_mfma_f64_16x16x4_f64): a complex product of the basis with the batch is
-// two real ones against the columns (psi_re, psi_im) and (psi_im, -psi_re) of
-// every right-hand side, two columns per vector, so 12 vectors take two
-// 16-column tiles and up to 8 take one.  Even one vector (2 of 16 columns)
-// leaves the matrix cores ahead of the memory: 1 KB of the basis per 128
-// cycles and SIMD is 18 TB/s.
+// All three are contractions in FP64.  From three vectors on, block_dot and the
+// projection run on the FP64 matrix cores (v_mfma_f64_16x16x4_f64): a complex
+// product of the basis with the batch is two real ones against the columns
+// (psi_re, psi_im) and (psi_im, -psi_re) of every right-hand side, two columns per
+// vector, so 12 vectors take two 16-column tiles and up to 8 take one.  One and two
+// vectors are bound by the basis alone and take FP64 FMAs.
 #include <algorithm>
 #include <string>
 
@@ -68,19 +67,20 @@ constexpr int PJ_PAD = 33;   // padded row of a unit in LDS
 // partial[(kb*ell + i)*R + r] = sum over K-block kb's units of conj(V_i) psi_r.
 // A unit is 32 sites of one row; a block of NW waves runs through a
 // contiguous range of units, wave w for the mw <= 16 modes from (blockIdx.x NW
-// + w) mw (rows past them repeat the last mode).  The matrix instruction wants 16 modes side by side, memory wants one:
-// a load that touches 16 modes (64 or 128 bytes of each) reached 2.6 TB/s,
-// whatever was in flight, so a wave loads 512 bytes of two modes at a time
-// into registers (the next unit, while the current one is used) and turns the
-// unit in its own part of LDS (units of 64 sites leave room for one block of
-// four waves a CU: 50 modes at 16^3x32 took 315 us against 238).  The batch's unit is shared by the block, in two
-// buffers, so one barrier per unit is enough.  The rows of a site tile follow
-// each other, so the batch's 16-byte blocks, which hold several rows, come
-// from cache.
+// + w) mw (rows past them repeat the last mode; skipping their loads puts
+// branches between the loads: 3 and 4 vectors, 20 modes, a third slower).  The
+// matrix instruction wants 16 modes side by side, memory wants one: a load that
+// touches 16 modes (64 or 128 bytes of each) reached 2.6 TB/s, whatever was in
+// flight, so a wave loads 512 bytes of two modes at a time into registers (the
+// next unit, while the current one is used) and turns the unit in its own part
+// of LDS (units of 64 sites leave room for one block of four waves a CU: 50
+// modes at 16^3x32 took 315 us against 238).  The batch's unit is shared by the
+// block, in two buffers, so one barrier per unit is enough.  The rows of a site
+// tile follow each other, so the batch's 16-byte blocks, which hold several
+// rows, come from cache.
 // 24^3x64, 100 modes, 12 F16 vectors: 5.42 ms with FP64 FMAs on an LDS copy of
 // the batch (LDS-bound: one 16-byte read per 8 FMAs), 3.59 ms now; the basis is
-// 17 GB, 2.7 ms at 6.35 TB/s, the matrix instructions 2.2 ms.  One FP64
-// vector: 2.65 ms, at the memory's rate.
+// 17 GB, 2.7 ms at 6.35 TB/s, the matrix instructions 2.2 ms.
 template <int P, int NW, int NT>
 __global__ __launch_bounds__(NW * 64) void dot_kernel(int Nh, int ell, int mw, const char* V, size_t vstrideV,
                                                       const char* psi, size_t vstrideP, int R, double2* partial) {
@@ -159,6 +159,91 @@ __global__ __launch_bounds__(NW * 64) void dot_kernel(int Nh, int ell, int mw, c
     for (int v = 0; v < 4; ++v) {
       const int i = i0 + q + 4 * v, col = 16 * n + j;
       if (q + 4 * v < mw && i < ell && col < 2 * R) out[static_cast<size_t>(i) * R * 2 + col] = acc[0][n][v] + acc[1][n][v];
+    }
+}
+
+// The same for one or two vectors with FP64 FMAs: 2 or 4 of the matrix
+// instruction's 16 columns would be used, and a wave with 9 modes of 16 loads as
+// long as one with 16.  A wave runs through the units (64 sites of one row) of
+// its block for IW modes, 1 KB of each at a time, the next unit in flight; the
+// batch's elements, the same for all waves of the block, come through L1.  No LDS
+// and no barrier.  Bound by the basis, 6.5-6.8 TB/s.  FP64, one vector (two), with
+// dot_kernel and with this, us: 24^3x64, 33 modes 1203 -> 839 (1218 -> 913), 100
+// modes 2611 -> 2556 (2612 -> 2677), 130 modes 4233 -> 3369 (4235 -> 3518);
+// 16^3x32, 33 modes 190 -> 128, 100 modes 403 -> 382; 8^3x16, 33 modes 18.7 -> 14.2.
+template <int P, int R, int IW>
+__global__ __launch_bounds__(512) void dot_small_kernel(int Nh, int ell, const char* V, size_t vstrideV,
+                                                        const char* psi, size_t vstrideP, double2* partial) {
+  using real = typename Prec<P>::real;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i0 = (blockIdx.x * (blockDim.x >> 6) + wave) * IW;
+  if (i0 >= ell) return;
+  const long units = 24L * ((Nh + 63) / 64);
+  const int u0 = static_cast<int>(units * blockIdx.y / gridDim.y);
+  const int u1 = static_cast<int>(units * (blockIdx.y + 1) / gridDim.y);
+  Cx<double> acc[IW][R], va[2][IW];
+  Cx<real> pa[2][R];
+  bool in[2];
+#pragma unroll
+  for (int m = 0; m < IW; ++m)
+#pragma unroll
+    for (int r = 0; r < R; ++r) acc[m][r] = {0.0, 0.0};
+  auto request = [&](int d, int u) {
+    const int row = u % 24, h0 = u / 24 * 64, l = min(lane, Nh - 1 - h0);
+    in[d] = lane == l;
+    const char* v = V + (static_cast<size_t>(row) * Nh + h0) * 16;
+#pragma unroll
+    for (int m = 0; m < IW; ++m)  // past the last mode: the basis' first line
+      va[d][m] = load_basis_at((i0 + m < ell ? v + static_cast<size_t>(i0 + m) * vstrideV : V) +
+                               static_cast<uint32_t>(i0 + m < ell ? l * 16 : 0));
+    const char* p = psi + cx_offset<P>(row, h0, Nh);
+#pragma unroll
+    for (int r = 0; r < R; ++r) pa[d][r] = ScalarIO<P>::load1(p + r * vstrideP + static_cast<uint32_t>(l * 16));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto use = [&](int d) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const double re = in[d] ? static_cast<double>(pa[d][r].re) : 0.0;
+      const double im = in[d] ? static_cast<double>(pa[d][r].im) : 0.0;
+#pragma unroll
+      for (int m = 0; m < IW; ++m) {
+        Cx<double>& a = acc[m][r];
+        a.re = fma(va[d][m].re, re, a.re);
+        a.im = fma(va[d][m].re, im, a.im);
+        a.re = fma(va[d][m].im, im, a.re);
+        a.im = fma(-va[d][m].im, re, a.im);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  int u = u0;
+  if (u < u1) request(0, u);
+  for (; u + 2 < u1; u += 2) {
+    request(1, u + 1);
+    use(0);
+    request(0, u + 2);
+    use(1);
+  }
+  if (u + 1 < u1) {
+    request(1, u + 1);
+    use(0);
+    use(1);
+  } else if (u < u1) {
+    use(0);
+  }
+#pragma unroll
+  for (int m = 0; m < IW; ++m)
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      double re = acc[m][r].re, im = acc[m][r].im;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        re += __shfl_xor(re, o, 64);
+        im += __shfl_xor(im, o, 64);
+      }
+      if (lane == 0 && i0 + m < ell)
+        partial[(static_cast<size_t>(blockIdx.y) * ell + i0 + m) * R + r] = make_double2(re, im);
     }
 }
 
@@ -495,15 +580,41 @@ __global__ __launch_bounds__(256) void rotate_kernel(int Nh, int K, int k, char*
 }
 
 // Waves of a dot_kernel block: the tiles of 16 modes in equal groups of at most
-// eight (each group reads the batch again), rounded up to an instantiation.
+// eight (each group reads the batch again).  A wave loads as long for a part of a
+// tile as for a whole one, so 3, 5 and 6 waves have kernels of their own: 24^3x64,
+// FP64, 4 vectors, 33 modes 1238 us with 4 waves, 1056 with 3; 130 modes 4310 with
+// twice 7, 3692 with twice 5; 12 vectors, 80 modes 3490 with 7, 3316 with 5 (F16 12
+// vectors, 72 modes, where the matrix instructions weigh more: 3210 and 3360).
 int dot_waves(int ell) {
-  const int tiles = (ell + 15) / 16, groups = (tiles + 7) / 8, nw = (tiles + groups - 1) / groups;
-  return nw <= 2 ? nw : nw <= 4 ? 4 : nw <= 7 ? 7 : 8;
+  const int tiles = (ell + 15) / 16, groups = (tiles + 7) / 8;
+  return (tiles + groups - 1) / groups;
 }
 
-// K-blocks of block_dot: what the 256 CUs hold at once (by LDS), and at least
-// four units each, which cost less than the partial sums of more blocks.
-int dot_blocks(const ovl_geom* g, int ell) {
+// Batches up to this take dot_small_kernel.  With two vectors dot_kernel is ahead by
+// 2% at 100 modes already, where its tiles are full, and behind by 4-33% elsewhere.
+constexpr int DOT_SMALL_R = 2;
+
+// Modes a wave and waves a block of dot_small_kernel: groups of at most 64 modes
+// (each reads the batch again), spread evenly over up to eight waves.
+void dot_small_split(int ell, int& iw, int& nw, int& groups) {
+  groups = (ell + 63) / 64;
+  iw = (ell + 8 * groups - 1) / (8 * groups);
+  nw = ((ell + groups - 1) / groups + iw - 1) / iw;
+  groups = (ell + iw * nw - 1) / (iw * nw);
+}
+
+// K-blocks of block_dot: what the 256 CUs hold at once (dot_small_kernel: 16 waves a
+// CU, as eight modes of one vector leave registers for; a third more blocks than
+// that made a second, nearly empty round: 24^3x64, 20 modes 615 against 530 us;
+// dot_kernel: by LDS), and at least four units each, which cost less than the
+// partial sums of more blocks.
+int dot_blocks(const ovl_geom* g, int ell, int R) {
+  if (R <= DOT_SMALL_R) {
+    int iw, nw, groups;
+    dot_small_split(ell, iw, nw, groups);
+    const long units = 24L * ((g->geo.Nh + 63) / 64);
+    return static_cast<int>(std::max(1L, std::min((units + 3) / 4, 256L * (16 / nw) / groups)));
+  }
   const long units = 24L * ((g->geo.Nh + PJ_TILE - 1) / PJ_TILE);
   const int nw = dot_waves(ell), groups = (ell + 16 * nw - 1) / (16 * nw);
   const long held = 256L * ((160 << 10) / ((nw * 16 + 2 * OVL_MAX_RHS) * PJ_PAD * 16));
@@ -517,15 +628,22 @@ void dot_go(const ovl_geom* g, const void* V, int ell, const void* psi, int R, d
                      static_cast<const char*>(psi), spinor_vec_bytes(g, P), R, part);
 }
 
-template <int P, int NT>
+template <int P, int NT, int NW = 8>
 void dot_mt(const ovl_geom* g, const void* V, int ell, const void* psi, int R, double2* part, int G, hipStream_t s) {
-  switch (dot_waves(ell)) {
-    case 1: dot_go<P, 1, NT>(g, V, ell, psi, R, part, G, s); break;
-    case 2: dot_go<P, 2, NT>(g, V, ell, psi, R, part, G, s); break;
-    case 4: dot_go<P, 4, NT>(g, V, ell, psi, R, part, G, s); break;
-    case 7: dot_go<P, 7, NT>(g, V, ell, psi, R, part, G, s); break;
-    default: dot_go<P, 8, NT>(g, V, ell, psi, R, part, G, s); break;
-  }
+  if constexpr (NW > 1)
+    if (dot_waves(ell) < NW) return dot_mt<P, NT, NW - 1>(g, V, ell, psi, R, part, G, s);
+  dot_go<P, NW, NT>(g, V, ell, psi, R, part, G, s);
+}
+
+template <int P, int R, int IW = 8>
+void dot_small_go(const ovl_geom* g, const void* V, int ell, const void* psi, double2* part, int G, hipStream_t s) {
+  int iw, nw, groups;
+  dot_small_split(ell, iw, nw, groups);
+  if constexpr (IW > 1)
+    if (iw < IW) return dot_small_go<P, R, IW - 1>(g, V, ell, psi, part, G, s);
+  hipLaunchKernelGGL((dot_small_kernel<P, R, IW>), dim3(groups, G), dim3(64 * nw), 0, s, g->geo.Nh, ell,
+                     static_cast<const char*>(V), spinor_vec_bytes(g, OVL_F64), static_cast<const char*>(psi),
+                     spinor_vec_bytes(g, P), part);
 }
 
 // C = V^dag psi with the per-block partials in `part` (ell * G * R entries).
@@ -533,7 +651,9 @@ void dot_prec(const ovl_geom* g, const void* V, int ell, const void* psi, int pr
               int G, hipStream_t s) {
   auto go = [&](auto P) {
     constexpr int p = decltype(P)::value;
-    if (R <= 8) dot_mt<p, 1>(g, V, ell, psi, R, part, G, s);
+    if (R == 1) dot_small_go<p, 1>(g, V, ell, psi, part, G, s);
+    else if (R == 2) dot_small_go<p, 2>(g, V, ell, psi, part, G, s);
+    else if (R <= 8) dot_mt<p, 1>(g, V, ell, psi, R, part, G, s);
     else dot_mt<p, 2>(g, V, ell, psi, R, part, G, s);
   };
   switch (prec) {
@@ -589,7 +709,7 @@ void sweep_prec(const ovl_geom* g, const void* V, int ell, const void* in, void*
 void block_dot(const ovl_geom* g, const void* V, int ell, const void* psi, int prec, int R, double2* C,
                hipStream_t s) {
   OVL_REQUIRE(R >= 1 && R <= OVL_MAX_RHS && ell >= 1, OVL_E_ARG, "block_dot: 1 <= R <= 12, ell >= 1");
-  const int G = dot_blocks(g, ell);
+  const int G = dot_blocks(g, ell, R);
   WsBuf part(static_cast<size_t>(ell) * G * R * sizeof(double2), s);
   dot_prec(g, V, ell, psi, prec, R, C, static_cast<double2*>(part.p), G, s);
 }
@@ -772,7 +892,7 @@ void lowmode_project(const ovl_lowmodes* lm, const void* psi, void* psih, void* 
                      hipStream_t s) {
   OVL_REQUIRE(nrhs >= 1 && nrhs <= OVL_MAX_RHS, OVL_E_ARG, "projection supports 1 to 12 right-hand sides");
   WsBuf cbuf(static_cast<size_t>(lm->ell) * nrhs * sizeof(double2), s);
-  const int G = dot_blocks(&lm->geom, lm->ell);
+  const int G = dot_blocks(&lm->geom, lm->ell, nrhs);
   WsBuf part(static_cast<size_t>(lm->ell) * G * nrhs * sizeof(double2), s);
   lowmode_project_ws(lm, psi, psih, w, prec, nrhs, g5w, static_cast<double2*>(cbuf.p),
                      static_cast<double2*>(part.p), G, s);
@@ -793,7 +913,7 @@ void lowmode_project_static(const ovl_lowmodes* lm, const void* psi, void* psih,
   const size_t unit = static_cast<size_t>(lm->ell) * nrhs * sizeof(double2);  // one coefficient set
   const size_t c_bytes = (unit + 255) / 256 * 256;
   const size_t fit = (kStaticScratchBytes - c_bytes) / unit;  // >= kStaticMinBlocks by the check above
-  const int G = static_cast<int>(std::min<size_t>(dot_blocks(&lm->geom, lm->ell), fit));
+  const int G = static_cast<int>(std::min<size_t>(dot_blocks(&lm->geom, lm->ell, nrhs), fit));
   char* base = static_cast<char*>(static_scratch());
   lowmode_project_ws(lm, psi, psih, w, prec, nrhs, 0, reinterpret_cast<double2*>(base),
                      reinterpret_cast<double2*>(base + c_bytes), G, s);

@@ -228,3 +228,33 @@ def test_projection_of_few_vectors(prec, dims):
                 for dev, want in ((h, want_h), (w, want_w)):
                     got = np.reshape(gu.unpack(g, dev, prec, nrhs), (nrhs, -1))
                     assert np.max(np.abs(got - want)) <= tol * max(1.0, np.max(np.abs(want))), (ell, nrhs, npos)
+
+
+@pytest.mark.parametrize("prec", [ovl.OVL_F64, ovl.OVL_F32, ovl.OVL_F16, ovl.OVL_BF16])
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (4, 4, 4, 4), (6, 6, 2, 10)])
+def test_projection_waves_and_mode_groups(prec, dims):
+    """The inner products where their split changes: 3, 5 and 6 waves and two
+    groups of 5 of the matrix-core form; one and two vectors with 1 to 8 modes a
+    wave, waves and groups that are not full, one to three groups of 64 modes."""
+    g = ovl.Geometry(dims)
+    V = si.orthonormal_spinors(dims, 150, 23)
+    vdev = _lowmodes_dev(g, V)
+    Vm = V.reshape(150, -1)
+    psi = np.stack([si.gaussian_spinor(dims, 830 + r) for r in range(12)])
+    u = gu.UNIT_ROUNDOFF[prec]
+    rng = np.random.default_rng(4)
+    for ell, nrhs in ((33, 4), (48, 12), (65, 3), (80, 12), (81, 5), (96, 9), (129, 12), (145, 8), (5, 1), (9, 2),
+                      (20, 1), (33, 1), (57, 2), (64, 1), (64, 2), (65, 1), (66, 2), (128, 2), (129, 1), (143, 2)):
+        lam = rng.uniform(0.1, 0.5, ell) * rng.choice([-1.0, 1.0], ell)
+        lm = ovl.LowModes(g, vdev, lam)
+        inp = gu.pack(g, psi[:nrhs], prec, nrhs)
+        h, w = gu.empty_field(g, prec, nrhs), gu.empty_field(g, prec, nrhs)
+        ovl.ovl_lowmodes_project(lm, inp, h, w, prec, nrhs, None)
+        x = np.reshape(gu.unpack(g, inp, prec, nrhs), (nrhs, -1))
+        c = Vm[:ell].conj() @ x.T
+        want_h = x - (Vm[:ell].T @ c).T
+        want_w = (Vm[:ell].T @ (np.sign(lam)[:, None] * c)).T
+        tol = 1e-13 if prec == ovl.OVL_F64 else 2 * u  # FP64 sums, then the storage rounding
+        for dev, want in ((h, want_h), (w, want_w)):
+            got = np.reshape(gu.unpack(g, dev, prec, nrhs), (nrhs, -1))
+            assert np.max(np.abs(got - want)) <= tol * max(1.0, np.max(np.abs(want))), (ell, nrhs)
