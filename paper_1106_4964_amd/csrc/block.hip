@@ -288,25 +288,25 @@ __device__ inline void turn(double2 (&x)[4]) {
   __builtin_memcpy(x, d, sizeof(d));
 }
 
-// The second sweep.  MODE 0: Y_r = f sum_i V_i K_ir, 1: Y_r += the same,
-// 2: psi_h = psi - sum_i C_i V_i into Y and w = [gamma5] sum_i s_i C_i V_i.
+// The second sweep of a projection of three and more vectors:
+// psi_h = psi - sum_i C_i V_i and w = [gamma5] sum_i s_i C_i V_i.
 // A block of four waves makes the 16-byte output blocks u of 256 / cpb sites of
 // one parity; a wave the 64 sites of one complex row, four tiles of 16 sites,
 // which are the rows of the matrix product, against the coefficients' columns
 // (c_re, c_im) and (-c_im, c_re).  A step is four modes, each loaded as 1 KB by
 // one instruction and turned into (16 sites x 4 modes) by lane swaps (loads of
-// 256 bytes from each of four modes were a third slower).  MODE 2 sums the
-// modes of positive and of negative sign apart (order: first nsp steps of four
-// modes with s = +1, then the others, -1 filling up a step), which halves the
-// columns: psi_h = psi - (S+ + S-), w = S+ - S-.  The sums pass through LDS,
-// where the rows of a 16-byte block meet.
+// 256 bytes from each of four modes were a third slower).  The modes of positive
+// and of negative sign are summed apart (order: first nsp steps of four modes with
+// s = +1, then the others, -1 filling up a step), which halves the columns:
+// psi_h = psi - (S+ + S-), w = S+ - S-.  The sums pass through LDS, where the rows
+// of a 16-byte block meet.
 // 24^3x64, 100 modes, 12 F16 vectors: 4.93 ms with one thread per element and
 // FP64 FMAs (4-byte stores), 3.95 ms now.
-template <int P, int NT, int MODE>
-__global__ __launch_bounds__(256) void sweep_kernel(int Nh, int ell, const char* V, size_t vstrideV, const char* in,
-                                                    char* Y, char* w, size_t vstrideP, int R,
-                                                    const double2* __restrict__ coef, const int* __restrict__ order,
-                                                    int nsp, int ns, int g5w, double f) {
+template <int P, int NT>
+__global__ __launch_bounds__(256) void project_kernel(int Nh, const char* V, size_t vstrideV, const char* psi,
+                                                      char* psih, char* w, size_t vstrideP, int R,
+                                                      const double2* __restrict__ coef,
+                                                      const int* __restrict__ order, int nsp, int ns, int g5w) {
   constexpr int cpb = Prec<P>::cpb, NB = 12 / cpb, SG = 256 / cpb;  // sites per block
   constexpr int LD = 8 * NT + 9;  // padded row of the LDS exchange: 16 or 24 columns are used
   using real = typename Prec<P>::real;
@@ -332,11 +332,7 @@ __global__ __launch_bounds__(256) void sweep_kernel(int Nh, int ell, const char*
     int i[4];  // the modes of the next request, looked up one request ahead
     auto look = [&](int s) {
 #pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        i[m] = 4 * s + m;
-        if (MODE == 2) i[m] = order[i[m]];
-        else if (i[m] >= ell) i[m] = -1;
-      }
+      for (int m = 0; m < 4; ++m) i[m] = order[4 * s + m];
     };
     auto request = [&](int d, int s) {
 #pragma unroll
@@ -403,7 +399,7 @@ __global__ __launch_bounds__(256) void sweep_kernel(int Nh, int ell, const char*
         for (int v = 0; v < 4; ++v)
           if (n == 0 || j < 8) slot(t, n, v) = acc[t][n][v];
   };
-  // one output, 16-byte blocks put together from LDS: out = [base] + f sums
+  // one output, 16-byte blocks put together from LDS: out = [base] + sgn sums
   auto store = [&](const char* base, char* out, double sgn, bool lower) {
     __syncthreads();
     for (int k = threadIdx.x; k < R * SG; k += 256) {
@@ -423,103 +419,128 @@ __global__ __launch_bounds__(256) void sweep_kernel(int Nh, int ell, const char*
     }
   };
 
-  if constexpr (MODE == 2) {
-    // one copy of the loop for both signs; S+ waits in LDS
+  // one copy of the loop for both signs; S+ waits in LDS
 #pragma unroll 1
-    for (int side = 0; side < 2; ++side) {
-      sum(side ? nsp : 0, side ? ns : nsp, acc);
-      if (side == 0) park();
-    }
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int n = 0; n < NT; ++n)
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          if (n == 0 || j < 8) {
-            const double a = slot(t, n, v), b = acc[t][n][v];
-            slot(t, n, v) = a + b;
-            acc[t][n][v] = a - b;
-          }
-    store(in, Y, -1.0, false);
-    __syncthreads();
-    park();
-    store(nullptr, w, 1.0, g5w != 0);
-  } else {
-    sum(0, ns, acc);
-    park();
-    store(MODE == 1 ? Y : nullptr, Y, f, false);
+  for (int side = 0; side < 2; ++side) {
+    sum(side ? nsp : 0, side ? ns : nsp, acc);
+    if (side == 0) park();
   }
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int n = 0; n < NT; ++n)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (n == 0 || j < 8) {
+          const double a = slot(t, n, v), b = acc[t][n][v];
+          slot(t, n, v) = a + b;
+          acc[t][n][v] = a - b;
+        }
+  store(psi, psih, -1.0, false);
+  __syncthreads();
+  park();
+  store(nullptr, w, 1.0, g5w != 0);
 }
 
-// The same for one or two vectors, with FP64 FMAs: a thread is a site and one of
-// its 16-byte blocks of rows, and reads U modes ahead.  Bound by the basis: 8 FMAs
-// or fewer per 16 bytes need no matrix instruction, and without the LDS turn five
-// to six waves a SIMD fit instead of three.  Both readings together, one vector
-// (two), with sweep_kernel and with this: 16^3x32, 50 modes, F16 425 -> 406 us
-// (441 -> 418), FP32 445 -> 426 (460 -> 440), FP64 465 -> 460 (472 -> 471);
-// 24^3x64, 100 modes, F16 5.44 -> 5.39 ms, FP64 5.95 -> 5.91.
-template <int P, int R, int MODE>
-__global__ __launch_bounds__(256) void sweep_small_kernel(int Nh, int ell, const char* V, size_t vstrideV,
-                                                          const char* in, char* Y, char* w, size_t vstrideP,
-                                                          const double2* __restrict__ coef,
-                                                          const int* __restrict__ order, int nsp, int ns, int g5w,
-                                                          double f) {
-  constexpr int cpb = Prec<P>::cpb, NB = 12 / cpb, U = cpb == 1 ? 8 : cpb == 2 ? 4 : 2;
+// The FMA form of the second reading, for block_axpy (FP64 vectors) and for the
+// projection of one or two vectors: a thread is a site and one of its 16-byte
+// blocks of rows.  MODE 0: Y_r = f sum_i V_i K_ir, 1: Y_r += the same (f = +-1),
+// 2: the projection, as above.  Bound by the basis; the 4 R FMAs per 16 bytes reach
+// 13 TB/s at 12 vectors.  Where the lattice fills the CUs, one load in flight per
+// thread reads best, with the rows of a site tile in consecutive blocks: more
+// loads in flight wait on each other.  On small lattices U modes are read ahead
+// (DEEP).  FP64 update, 100 modes, us, with matrix instructions (1 and 2 vectors:
+// 8 modes ahead, some read twice), U modes ahead, one load:
+//              24^3x64           16^3x32          8^3x16
+//    1 vector  2944 2888 2765    427 423 386      25  24  49
+//    4         3397 3359 3328    483 467 431      29  26  56
+//   12         4022 4089 4110    606 581 528      44  36  67
+template <int P, int R, int MODE, bool DEEP>
+__global__ __launch_bounds__(256) void sweep_kernel(int Nh, int ell, const char* V, size_t vstrideV, const char* in,
+                                                    char* Y, char* w, size_t vstrideP,
+                                                    const double2* __restrict__ coef, const int* __restrict__ order,
+                                                    int nsp, int ns, int g5w, double f) {
+  constexpr int cpb = Prec<P>::cpb, NB = 12 / cpb, U = cpb == 1 ? (R <= 4 ? 8 : 4) : cpb == 2 ? 4 : 2;
   using real = typename Prec<P>::real;
-  const int h = blockIdx.x * 256 + threadIdx.x, pu = blockIdx.y;  // pu = p NB + u
+  const int tiles = (Nh + 255) / 256, b = blockIdx.x;
+  const int pu = DEEP ? b / tiles : b % (2 * NB);  // p NB + u
+  const int h = (DEEP ? b % tiles : b / (2 * NB)) * 256 + threadIdx.x;
   if (h >= Nh) return;
   V += static_cast<size_t>(pu * cpb) * Nh * 16;
   const uint32_t hoff = static_cast<uint32_t>(h) * 16u;
+  const size_t off = (static_cast<size_t>(pu) * Nh + h) * 16;
   Cx<double> acc[2][R][cpb];
 #pragma unroll
-  for (int r = 0; r < R; ++r)
+  for (int r = 0; r < R; ++r) {
+    Cx<real> y[cpb];
+    if (MODE == 1) Block<P>::load(Y + r * vstrideP + off, y);
 #pragma unroll
-    for (int c = 0; c < cpb; ++c) acc[0][r][c] = acc[1][r][c] = {0.0, 0.0};
+    for (int c = 0; c < cpb; ++c) {
+      acc[0][r][c] = acc[1][r][c] = {0.0, 0.0};
+      if (MODE == 1) acc[0][r][c] = {f * static_cast<double>(y[c].re), f * static_cast<double>(y[c].im)};
+    }
+  }
   auto sum = [&](int k0, int k1, Cx<double> (*a)[cpb]) {
     if (MODE == 2)
       while (k1 > k0 && order[k1 - 1] < 0) --k1;  // the padding of the last quad
     auto mode = [&](int k) { return MODE == 2 ? order[k] : k; };
     Cx<double> va[2][U][cpb];
+    auto load = [&](Cx<double>* x, int k) {
+      const char* v = V + static_cast<size_t>(mode(k)) * vstrideV;
+#pragma unroll
+      for (int c = 0; c < cpb; ++c) x[c] = load_basis_at(v + static_cast<size_t>(c) * Nh * 16 + hoff);
+    };
+    auto add = [&](const Cx<double>* x, int k) {
+      const double2* cm = coef + mode(k) * R;
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int c = 0; c < cpb; ++c) {
+          Cx<double>& y = a[r][c];
+          y.re = fma(x[c].re, cm[r].x, y.re);
+          y.im = fma(x[c].re, cm[r].y, y.im);
+          y.re = fma(-x[c].im, cm[r].y, y.re);
+          y.im = fma(x[c].im, cm[r].x, y.im);
+        }
+    };
     auto request = [&](int d, int k) {
 #pragma unroll
-      for (int m = 0; m < U; ++m) {
-        const char* v = V + static_cast<size_t>(mode(min(k + m, k1 - 1))) * vstrideV;
-#pragma unroll
-        for (int c = 0; c < cpb; ++c) va[d][m][c] = load_basis_at(v + static_cast<size_t>(c) * Nh * 16 + hoff);
-      }
+      for (int m = 0; m < U; ++m) load(va[d][m], k + m);
+      __builtin_amdgcn_sched_barrier(0);
     };
     auto use = [&](int d, int k) {
 #pragma unroll
-      for (int m = 0; m < U; ++m) {
-        if (k + m >= k1) break;
-        const double2* cm = coef + mode(k + m) * R;
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-          for (int c = 0; c < cpb; ++c) {
-            Cx<double>& x = a[r][c];
-            const Cx<double> v = va[d][m][c];
-            x.re = fma(v.re, cm[r].x, x.re);
-            x.im = fma(v.re, cm[r].y, x.im);
-            x.re = fma(-v.im, cm[r].y, x.re);
-            x.im = fma(v.im, cm[r].x, x.im);
-          }
-      }
+      for (int m = 0; m < U; ++m) add(va[d][m], k + m);
+      __builtin_amdgcn_sched_barrier(0);
     };
-    if (k0 >= k1) return;
-    request(0, k0);
-    for (int k = k0; k < k1; k += 2 * U) {
-#pragma unroll
-      for (int d = 0; d < 2; ++d) {
-        request(1 - d, k + (d + 1) * U);
-        __builtin_amdgcn_sched_barrier(0);
-        use(d, k + d * U);
-        __builtin_amdgcn_sched_barrier(0);
+    if (!DEEP) {
+#pragma unroll 1
+      for (int k = k0; k < k1; ++k) {
+        load(va[0][0], k);
+        add(va[0][0], k);
       }
+      return;
     }
+    // the modes past the last whole group first, then group after group
+    const int rest = (k1 - k0) % U;
+    int k = k0 + rest, n = (k1 - k0) / U;
+#pragma unroll
+    for (int m = 0; m < U - 1; ++m)
+      if (m < rest) load(va[0][m], k0 + m);
+    if (n > 0) request(1, k);
+#pragma unroll
+    for (int m = 0; m < U - 1; ++m)
+      if (m < rest) add(va[0][m], k0 + m);
+    for (; n > 2; n -= 2, k += 2 * U) {
+      request(0, k + U);
+      use(1, k);
+      request(1, k + 2 * U);
+      use(0, k + U);
+    }
+    if (n == 2) request(0, k + U);
+    if (n > 0) use(1, k);
+    if (n == 2) use(0, k + U);
   };
-  const size_t off = (static_cast<size_t>(pu) * Nh + h) * 16;
   auto store = [&](const char* base, char* out, Cx<double> (*a)[cpb], double sgn, bool lower) {
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -549,7 +570,7 @@ __global__ __launch_bounds__(256) void sweep_small_kernel(int Nh, int ell, const
     store(nullptr, w, acc[1], 1.0, g5w != 0);
   } else {
     sum(0, ell, acc[0]);
-    store(MODE == 1 ? Y : nullptr, Y, acc[0], f, false);
+    store(nullptr, Y, acc[0], f, false);
   }
 }
 
@@ -669,39 +690,51 @@ void dot_prec(const ovl_geom* g, const void* V, int ell, const void* psi, int pr
   OVL_HIP(hipGetLastError());
 }
 
-template <int P, int MODE>
-void sweep_go(const ovl_geom* g, const void* V, int ell, const void* in, void* Y, void* w, int R, const double2* K,
+// One load in flight per thread needs the CUs full of waves: 24 rows of 16 Ki sites
+// are three quarters of what they hold (FP64 update, 1 vector, 100 modes, ahead / one
+// load: 10^3x20, 960 blocks, 0.93 / 1.00; 12^3x24, 1944 blocks, 1.09 / 1.00).
+bool sweep_deep(int Nh) { return Nh < 16384; }
+
+template <int P, int R, int MODE>
+void sweep_go(const ovl_geom* g, const void* V, int ell, const void* in, void* Y, void* w, const double2* K,
               const int* order, int nsp, int ns, int g5w, double f, hipStream_t s) {
-  constexpr int cpb = Prec<P>::cpb;
-  const int Nh = g->geo.Nh, blocks = 2 * (12 / cpb) * ((Nh + 256 / cpb - 1) / (256 / cpb));
+  const int Nh = g->geo.Nh;
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, Nh, ell, static_cast<const char*>(V),
-                       spinor_vec_bytes(g, OVL_F64), static_cast<const char*>(in), static_cast<char*>(Y),
-                       static_cast<char*>(w), spinor_vec_bytes(g, P), R, K, order, nsp, ns, g5w, f);
+    hipLaunchKernelGGL(kernel, dim3((Nh + 255) / 256 * (24 / Prec<P>::cpb)), dim3(256), 0, s, Nh, ell,
+                       static_cast<const char*>(V), spinor_vec_bytes(g, OVL_F64), static_cast<const char*>(in),
+                       static_cast<char*>(Y), static_cast<char*>(w), spinor_vec_bytes(g, P), K, order, nsp, ns, g5w, f);
   };
-  auto small = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3((Nh + 255) / 256, 24 / cpb), dim3(256), 0, s, Nh, ell, static_cast<const char*>(V),
-                       spinor_vec_bytes(g, OVL_F64), static_cast<const char*>(in), static_cast<char*>(Y),
-                       static_cast<char*>(w), spinor_vec_bytes(g, P), K, order, nsp, ns, g5w, f);
-  };
-  if (R <= 2) {  // FMAs do where the matrix instruction would use 2 or 4 of its 16 columns
-    if (R == 1) small(sweep_small_kernel<P, 1, MODE>);
-    else small(sweep_small_kernel<P, 2, MODE>);
-  } else if (R <= 8) go(sweep_kernel<P, 1, MODE>);
-  else go(sweep_kernel<P, 2, MODE>);
+  if (sweep_deep(Nh)) go(sweep_kernel<P, R, MODE, true>);
+  else go(sweep_kernel<P, R, MODE, false>);
   OVL_HIP(hipGetLastError());
 }
 
-template <int MODE>
-void sweep_prec(const ovl_geom* g, const void* V, int ell, const void* in, void* Y, void* w, int prec, int R,
-                const double2* K, const int* order, int nsp, int ns, int g5w, double f, hipStream_t s) {
-  switch (prec) {
-    case OVL_F64: sweep_go<OVL_F64, MODE>(g, V, ell, in, Y, w, R, K, order, nsp, ns, g5w, f, s); break;
-    case OVL_F32: sweep_go<OVL_F32, MODE>(g, V, ell, in, Y, w, R, K, order, nsp, ns, g5w, f, s); break;
-    case OVL_F16: sweep_go<OVL_F16, MODE>(g, V, ell, in, Y, w, R, K, order, nsp, ns, g5w, f, s); break;
-    case OVL_BF16: sweep_go<OVL_BF16, MODE>(g, V, ell, in, Y, w, R, K, order, nsp, ns, g5w, f, s); break;
-    default: throw Error(OVL_E_PRECISION, "unknown precision");
-  }
+// Y_r = [Y_r] + f sum_i V_i K_ir for FP64 vectors.
+template <int MODE, int R = OVL_MAX_RHS>
+void update(const ovl_geom* g, const void* V, int ell, void* Y, int nrhs, const double2* K, double f, hipStream_t s) {
+  if constexpr (R > 1)
+    if (nrhs < R) return update<MODE, R - 1>(g, V, ell, Y, nrhs, K, f, s);
+  sweep_go<OVL_F64, R, MODE>(g, V, ell, nullptr, Y, nullptr, K, nullptr, 0, 0, 0, f, s);
+}
+
+template <int P>
+void project_go(const ovl_lowmodes* lm, const void* psi, void* psih, void* w, int R, const double2* C, int g5w,
+                hipStream_t s) {
+  const ovl_geom* g = &lm->geom;
+  if (R == 1)
+    return sweep_go<P, 1, 2>(g, lm->V, lm->ell, psi, psih, w, C, lm->dev_order, lm->steps_pos, lm->steps, g5w, 1.0, s);
+  if (R == 2)
+    return sweep_go<P, 2, 2>(g, lm->V, lm->ell, psi, psih, w, C, lm->dev_order, lm->steps_pos, lm->steps, g5w, 1.0, s);
+  constexpr int cpb = Prec<P>::cpb;
+  const int Nh = g->geo.Nh, blocks = 2 * (12 / cpb) * ((Nh + 256 / cpb - 1) / (256 / cpb));
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, Nh, static_cast<const char*>(lm->V),
+                       spinor_vec_bytes(g, OVL_F64), static_cast<const char*>(psi), static_cast<char*>(psih),
+                       static_cast<char*>(w), spinor_vec_bytes(g, P), R, C, lm->dev_order, lm->steps_pos, lm->steps, g5w);
+  };
+  if (R <= 8) go(project_kernel<P, 1>);
+  else go(project_kernel<P, 2>);
+  OVL_HIP(hipGetLastError());
 }
 
 }  // namespace
@@ -714,12 +747,11 @@ void block_dot(const ovl_geom* g, const void* V, int ell, const void* psi, int p
   dot_prec(g, V, ell, psi, prec, R, C, static_cast<double2*>(part.p), G, s);
 }
 
-void block_axpy(const ovl_geom* g, const void* V, int ell, const double2* K, void* Y, int prec, int R, bool keep,
+void block_axpy(const ovl_geom* g, const void* V, int ell, const double2* K, void* Y, int R, bool keep,
                 hipStream_t s) {
   OVL_REQUIRE(R >= 1 && R <= OVL_MAX_RHS && ell >= 1, OVL_E_ARG, "block_axpy: 1 <= R <= 12, ell >= 1");
-  const int ns = (ell + 3) / 4;
-  if (keep) sweep_prec<1>(g, V, ell, nullptr, Y, nullptr, prec, R, K, nullptr, ns, ns, 0, 1.0, s);
-  else sweep_prec<0>(g, V, ell, nullptr, Y, nullptr, prec, R, K, nullptr, ns, ns, 0, 1.0, s);
+  if (keep) update<1>(g, V, ell, Y, R, K, 1.0, s);
+  else update<0>(g, V, ell, Y, R, K, 1.0, s);
 }
 
 namespace {
@@ -743,10 +775,9 @@ void lanczos_step(const ovl_geom* g, const void* Q, int n, void* w, void* next, 
   double2 *c1 = scratch, *c2 = scratch + n;
   double* sc = reinterpret_cast<double*>(scratch + 2 * n);  // norm (2), 1 / beta (2)
   const size_t v64 = spinor_vec_bytes(g, OVL_F64);
-  const int ns = (n + 3) / 4;
   for (double2* c : {c1, c2}) {
     block_dot(g, Q, n, w, OVL_F64, 1, c, s);
-    sweep_prec<1>(g, Q, n, nullptr, w, nullptr, OVL_F64, 1, c, nullptr, ns, ns, 0, -1.0, s);
+    update<1>(g, Q, n, w, 1, c, -1.0, s);
   }
   blas_norm2(OVL_F64, v64 / 16, w, 1, v64, sc, s);
   hipLaunchKernelGGL(lanczos_scalars_kernel, dim3(1), dim3(256), 0, s, n, c1, c2, coef, sc, beta, sc + 2);
@@ -824,8 +855,7 @@ void lanczos_fused(const ovl_geom* g, void* Q, int j, bool last, double* alpha, 
   block_dot(g, Q, j + 1, u, OVL_F64, last ? 1 : 2, scratch, s);
   if (last) return scalars(lanczos_fused_scalars_kernel<1>);
   scalars(lanczos_fused_scalars_kernel<2>);
-  const int ns = (j + 3) / 4;
-  if (j > 0) sweep_prec<1>(g, Q, j, nullptr, u, nullptr, OVL_F64, 2, scratch, nullptr, ns, ns, 0, -1.0, s);
+  if (j > 0) update<1>(g, Q, j, u, 2, scratch, -1.0, s);
   const size_t n = v64 / 16;
   hipLaunchKernelGGL(lanczos_next_kernel, dim3(static_cast<unsigned>(std::min<size_t>((n + 255) / 256, 8192))),
                      dim3(256), 0, s, n, sc, reinterpret_cast<double2*>(u), reinterpret_cast<double2*>(u + v64));
@@ -851,8 +881,13 @@ void lowmode_project_ws(const ovl_lowmodes* lm, const void* psi, void* psih, voi
   OVL_REQUIRE(nrhs >= 1 && nrhs <= OVL_MAX_RHS && lm->ell >= 1, OVL_E_ARG,
               "projection: 1 <= nrhs <= 12 and at least one low mode");
   dot_prec(&lm->geom, lm->V, lm->ell, psi, prec, nrhs, C, part, G, s);
-  sweep_prec<2>(&lm->geom, lm->V, lm->ell, psi, psih, w, prec, nrhs, C, lm->dev_order, lm->steps_pos, lm->steps, g5w,
-                1.0, s);
+  switch (prec) {
+    case OVL_F64: project_go<OVL_F64>(lm, psi, psih, w, nrhs, C, g5w, s); break;
+    case OVL_F32: project_go<OVL_F32>(lm, psi, psih, w, nrhs, C, g5w, s); break;
+    case OVL_F16: project_go<OVL_F16>(lm, psi, psih, w, nrhs, C, g5w, s); break;
+    case OVL_BF16: project_go<OVL_BF16>(lm, psi, psih, w, nrhs, C, g5w, s); break;
+    default: throw Error(OVL_E_PRECISION, "unknown precision");
+  }
 }
 
 // Scratch of the allocation-free projection: one array per GPU, in device

@@ -233,7 +233,7 @@ void rotate(const ovl_geom* g, const void* V, int m, const std::vector<zc>& M, i
         host[i * R + r] = make_double2(v.real(), v.imag());
       }
     OVL_HIP(hipMemcpyAsync(kb.p, host.data(), sizeof(double2) * m * R, hipMemcpyHostToDevice, s));
-    block_axpy(g, V, m, static_cast<const double2*>(kb.p), vec(Y, v64, c0), OVL_F64, R, false, s);
+    block_axpy(g, V, m, static_cast<const double2*>(kb.p), vec(Y, v64, c0), R, false, s);
     OVL_HIP(hipStreamSynchronize(s));  // host staging buffer is reused
   }
 }

@@ -77,7 +77,7 @@ void blas_norm2(int prec, size_t n16, const void* x, int nrhs, size_t vstride, d
 // index i*R + r.
 void block_dot(const ovl_geom* g, const void* V, int ell, const void* psi, int prec, int R, double2* C,
                hipStream_t s);
-void block_axpy(const ovl_geom* g, const void* V, int ell, const double2* K, void* Y, int prec, int R, bool keep,
+void block_axpy(const ovl_geom* g, const void* V, int ell, const double2* K, void* Y, int R, bool keep,
                 hipStream_t s);
 // One Lanczos step's vector work, all on the stream: w -= Q (Q^dag w) twice for
 // the n FP64 vectors Q, coef[0..n) = the two passes' coefficients added, beta =

@@ -201,7 +201,7 @@ int ovl_overlap_eigs(const ovl_gauge* u, double rho, const ovl_sign* sgn, const 
             hc[i] = make_double2(-hc[i].x, -hc[i].y);
           }
           OVL_HIP(hipMemcpyAsync(cb.p, hc.data(), sizeof(double2) * (j + 1), hipMemcpyHostToDevice, s));
-          block_axpy(&hg, Q.p, j + 1, static_cast<const double2*>(cb.p), w.p, OVL_F64, 1, true, s);
+          block_axpy(&hg, Q.p, j + 1, static_cast<const double2*>(cb.p), w.p, 1, true, s);
           OVL_HIP(hipStreamSynchronize(s));
         }
         for (int i = 0; i <= j; ++i) Tat(i, j) = zc(hc2[i].x, hc2[i].y);
@@ -438,9 +438,9 @@ void deflate(const ovl_deflation* df, double rho, double m, void* x, void* r, in
     OVL_HIP(hipMemcpyAsync(dx.p, kx.data(), sizeof(double2) * kx.size(), hipMemcpyHostToDevice, s));
     OVL_HIP(hipMemcpyAsync(dz.p, kz.data(), sizeof(double2) * kz.size(), hipMemcpyHostToDevice, s));
     OVL_HIP(hipMemcpyAsync(dr.p, kr.data(), sizeof(double2) * kr.size(), hipMemcpyHostToDevice, s));
-    block_axpy(g, df->Xi, n, static_cast<const double2*>(dx.p), x, OVL_F64, R, true, s);
-    block_axpy(g, df->Z, n, static_cast<const double2*>(dz.p), r, OVL_F64, R, true, s);
-    block_axpy(g, df->Xi, n, static_cast<const double2*>(dr.p), r, OVL_F64, R, true, s);
+    block_axpy(g, df->Xi, n, static_cast<const double2*>(dx.p), x, R, true, s);
+    block_axpy(g, df->Z, n, static_cast<const double2*>(dz.p), r, R, true, s);
+    block_axpy(g, df->Xi, n, static_cast<const double2*>(dr.p), r, R, true, s);
     OVL_HIP(hipStreamSynchronize(s));  // the host coefficient arrays end with this scope
     return;
   }
@@ -461,8 +461,8 @@ void deflate(const ovl_deflation* df, double rho, double m, void* x, void* r, in
   WsBuf kx(sizeof(double2) * hx.size(), s), kr(sizeof(double2) * h.size(), s);
   OVL_HIP(hipMemcpyAsync(kx.p, hx.data(), sizeof(double2) * hx.size(), hipMemcpyHostToDevice, s));
   OVL_HIP(hipMemcpyAsync(kr.p, h.data(), sizeof(double2) * h.size(), hipMemcpyHostToDevice, s));
-  block_axpy(g, df->Xi, n, static_cast<const double2*>(kx.p), x, OVL_F64, R, true, s);
-  block_axpy(g, df->Xi, n, static_cast<const double2*>(kr.p), r, OVL_F64, R, true, s);
+  block_axpy(g, df->Xi, n, static_cast<const double2*>(kx.p), x, R, true, s);
+  block_axpy(g, df->Xi, n, static_cast<const double2*>(kr.p), r, R, true, s);
   OVL_HIP(hipStreamSynchronize(s));  // the host coefficient arrays end with this scope
 }
 

@@ -394,7 +394,7 @@ int ovl_rational_sign_apply(void* out, const void* in, const ovl_gauge* u, doubl
       for (int l = 0; l < n; ++l) bc[l] = make_double2(rat->b[l], 0.0);
       WsBuf bdev(sizeof(double2) * n, s);
       OVL_HIP(hipMemcpyAsync(bdev.p, bc.data(), sizeof(double2) * n, hipMemcpyHostToDevice, s));
-      block_axpy(g, X.p, n, static_cast<const double2*>(bdev.p), pq.p, OVL_F64, 1, false, s);
+      block_axpy(g, X.p, n, static_cast<const double2*>(bdev.p), pq.p, 1, false, s);
       OVL_HIP(hipStreamSynchronize(s));
     } else {
       // ------------------------------------------------ double pass

@@ -769,8 +769,8 @@ int fgcr_solve(void* x, const void* b, int R, const ovl_gauge* u, double rho, do
             block_dot(g, Wb.p, nb, w64.p, OVL_F64, R, static_cast<double2*>(Cb.p), s);
             hipLaunchKernelGGL(gcr_coef_kernel, dim3((nb * R + 255) / 256), dim3(256), 0, s, nb * R, R,
                                static_cast<const double2*>(Cb.p), static_cast<double2*>(Kb.p), dG);
-            block_axpy(g, Wb.p, nb, static_cast<const double2*>(Kb.p), w64.p, OVL_F64, R, true, s);
-            block_axpy(g, Zb.p, nb, static_cast<const double2*>(Kb.p), z64.p, OVL_F64, R, true, s);
+            block_axpy(g, Wb.p, nb, static_cast<const double2*>(Kb.p), w64.p, R, true, s);
+            block_axpy(g, Zb.p, nb, static_cast<const double2*>(Kb.p), z64.p, R, true, s);
           }
           // W_j = w / ||w||, Z_j = z / ||w||
           blas_norm2(OVL_F64, n16, w64.p, R, v64, dG->tmp, s);

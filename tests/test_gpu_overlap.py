@@ -258,3 +258,31 @@ def test_projection_waves_and_mode_groups(prec, dims):
         for dev, want in ((h, want_h), (w, want_w)):
             got = np.reshape(gu.unpack(g, dev, prec, nrhs), (nrhs, -1))
             assert np.max(np.abs(got - want)) <= tol * max(1.0, np.max(np.abs(want))), (ell, nrhs)
+
+
+@pytest.mark.parametrize("prec", [ovl.OVL_F64, ovl.OVL_F32, ovl.OVL_F16, ovl.OVL_BF16])
+@pytest.mark.parametrize("dims", [(16, 16, 16, 8), (14, 16, 18, 10), (10, 16, 18, 10)])
+def test_projection_of_few_vectors_on_larger_lattices(prec, dims):
+    """One and two vectors where one load per thread is in flight (from 16384
+    half-sites on: exactly, and with a remainder) and just below (14400), with one
+    sign or both."""
+    g = ovl.Geometry(dims)
+    V = si.orthonormal_spinors(dims, 9, 29)
+    vdev = _lowmodes_dev(g, V)
+    Vm = V.reshape(9, -1)
+    psi = np.stack([si.gaussian_spinor(dims, 860 + r) for r in range(2)])
+    u = gu.UNIT_ROUNDOFF[prec]
+    for ell, nrhs, npos in ((9, 1, 4), (9, 2, 1), (5, 2, 5), (1, 1, 0)):
+        lam = np.where(np.arange(ell) < npos, 0.2, -0.3)[::-1].copy()
+        lm = ovl.LowModes(g, vdev, lam)
+        inp = gu.pack(g, psi[:nrhs], prec, nrhs)
+        h, w = gu.empty_field(g, prec, nrhs), gu.empty_field(g, prec, nrhs)
+        ovl.ovl_lowmodes_project(lm, inp, h, w, prec, nrhs, None)
+        x = np.reshape(gu.unpack(g, inp, prec, nrhs), (nrhs, -1))
+        c = Vm[:ell].conj() @ x.T
+        want_h = x - (Vm[:ell].T @ c).T
+        want_w = (Vm[:ell].T @ (np.sign(lam)[:, None] * c)).T
+        tol = 1e-13 if prec == ovl.OVL_F64 else 2 * u  # FP64 sums, then the storage rounding
+        for dev, want in ((h, want_h), (w, want_w)):
+            got = np.reshape(gu.unpack(g, dev, prec, nrhs), (nrhs, -1))
+            assert np.max(np.abs(got - want)) <= tol * max(1.0, np.max(np.abs(want))), (ell, nrhs, npos)

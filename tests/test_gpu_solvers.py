@@ -503,3 +503,43 @@ def test_lanczos_bound_refuses_non_finite_links():
         ovl.ovl_hw_bound(gu.make_gauge(g, U), RHO, gu.pack(g, si.gaussian_spinor(dims, 3), ovl.OVL_F64), 5,
                          ctypes.byref(lam), None, None, None)
     assert e.value.name == "OVL_E_NAN" and lam.value == -1.0
+
+
+@pytest.mark.parametrize("dims", [(16, 16, 16, 8), (14, 16, 18, 10)])
+def test_block_updates_on_larger_lattices(dims):
+    """The eigensolver (updates of one vector, combinations of up to 12) and the
+    Lanczos bound (updates of two) on lattices that fill the GPU, exactly 16384
+    half-sites and a number that is no multiple of a block: eigenvectors by the
+    oracle's H_w, the bound's Ritz values by a Lanczos run of the oracle's."""
+    lat = Lattice(dims)
+    U = si.gauge_field(dims, 0.25, 2)
+    g = ovl.Geometry(dims)
+    gauge = gu.make_gauge(g, U)
+    steps = 12
+    lam, tmin, tmax = _bound(g, gauge, steps=steps, seed=17)
+    q = [si.gaussian_spinor(dims, 17).ravel()]
+    q[0] = q[0] / np.linalg.norm(q[0])
+    T = np.zeros((steps, steps))
+    for j in range(steps):
+        w = dirac.hw_apply(lat, U, q[j].reshape(g.N, 4, 3), RHO).ravel()
+        T[j, j] = np.vdot(q[j], w).real
+        for _ in range(2):
+            for v in q:
+                w = w - np.vdot(v, w) * v
+        b = np.linalg.norm(w)
+        if j + 1 < steps:
+            T[j, j + 1] = T[j + 1, j] = b
+            q.append(w / b)
+    th, S = np.linalg.eigh(T)
+    want = (max(abs(th[0]) + b * abs(S[-1, 0]), abs(th[-1]) + b * abs(S[-1, -1])), th[0], th[-1])
+    # twelve steps of FP64 sums over 4e5 numbers
+    assert np.allclose((lam, tmin, tmax), want, rtol=0, atol=1e-11)
+    ell, m = 3, 11
+    rc, V, ev, st = _eigs(g, gauge, ell, m, 6.6, tol=1e-10, degree=40)
+    assert rc == 0, (st.iterations, st.max_residual)
+    Vh = gu.unpack(g, V, ovl.OVL_F64, m)[:ell]
+    for i in range(ell):
+        r = dirac.hw_apply(lat, U, Vh[i], RHO) - ev[i] * Vh[i]
+        assert np.linalg.norm(r) <= 1.1e-10 * 6.6
+    G = Vh.reshape(ell, -1).conj() @ Vh.reshape(ell, -1).T
+    assert np.max(np.abs(G - np.eye(ell))) < 1e-13
