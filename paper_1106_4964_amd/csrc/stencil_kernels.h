@@ -638,16 +638,12 @@ void launch_k(const StencilArgs& A0, int nrhs, Shape sh, hipStream_t s) {
   }
   if (split) {
     dim3 grid(hblocks * A.npar, nrhs / sh.kr), block(256);
-    switch (sh.kr) {
-      case 1: hipLaunchKernelGGL((stencil_split_kernel<P, R, NV, 1>), grid, block, 0, s, A); break;
-      case 2: hipLaunchKernelGGL((stencil_split_kernel<P, R, NV, 2>), grid, block, 0, s, A); break;
-      case 3:
-        if constexpr (P != OVL_F64) hipLaunchKernelGGL((stencil_split_kernel<P, R, NV, 3>), grid, block, 0, s, A);
-        break;
-      case 4:
-        if constexpr (P != OVL_F64) hipLaunchKernelGGL((stencil_split_kernel<P, R, NV, 4>), grid, block, 0, s, A);
-        break;
-      default: throw Error(OVL_E_ARG, "stencil: unsupported vectors per thread");
+    OVL_REQUIRE(sh.kr >= 1 && sh.kr <= (P == OVL_F64 ? 2 : 4), OVL_E_ARG, "stencil: unsupported vectors per thread");
+    if (sh.kr == 1) hipLaunchKernelGGL((stencil_split_kernel<P, R, NV, 1>), grid, block, 0, s, A);
+    else if (sh.kr == 2) hipLaunchKernelGGL((stencil_split_kernel<P, R, NV, 2>), grid, block, 0, s, A);
+    if constexpr (P != OVL_F64) {
+      if (sh.kr == 3) hipLaunchKernelGGL((stencil_split_kernel<P, R, NV, 3>), grid, block, 0, s, A);
+      else if (sh.kr == 4) hipLaunchKernelGGL((stencil_split_kernel<P, R, NV, 4>), grid, block, 0, s, A);
     }
     return;
   }
