@@ -96,15 +96,6 @@ template <typename T>
 __host__ __device__ inline Cx<T> cmul_conj(Cx<T> a, Cx<T> b) {
   return {a.re * b.re + a.im * b.im, a.re * b.im - a.im * b.re};
 }
-// i*a and -i*a
-template <typename T>
-__host__ __device__ inline Cx<T> times_i(Cx<T> a) {
-  return {-a.im, a.re};
-}
-template <typename T>
-__host__ __device__ inline Cx<T> times_mi(Cx<T> a) {
-  return {a.im, -a.re};
-}
 
 // ------------------------------------------------------ storage formats
 // A storage format maps 12 complex numbers of compute type `real` to
@@ -116,19 +107,8 @@ struct bf16_t {
 __host__ __device__ inline float bf16_to_float(uint16_t b) {
   return __builtin_bit_cast(float, static_cast<uint32_t>(b) << 16);
 }
-// Round to nearest even; NaN stays a (quiet) NaN.  Written without a branch:
-// a data-dependent branch per stored element splits the stencil kernels into
-// many basic blocks and the register allocator then keeps every loaded
-// neighbour alive across them (256 VGPRs and spills instead of ~80).
-__host__ __device__ inline uint16_t float_to_bf16(float f) {
-  const uint32_t u = __builtin_bit_cast(uint32_t, f);
-  const uint32_t rounded = (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
-  const uint32_t quiet_nan = (u >> 16) | 0x40u;
-  return static_cast<uint16_t>(((u & 0x7fffffffu) > 0x7f800000u) ? quiet_nan : rounded);
-}
-
 // Two reals as a pair of bf16, round to nearest even: gfx950 converts a pair
-// in one instruction (v_cvt_pk_bf16_f32), where float_to_bf16 takes about
+// in one instruction (v_cvt_pk_bf16_f32), where integer arithmetic takes about
 // eight per real, a fifth of a BF16 stencil's arithmetic.
 __device__ inline uint32_t pack_bf16(float lo, float hi) {
   typedef float f32x2_t __attribute__((ext_vector_type(2)));
@@ -449,29 +429,6 @@ struct LinkRaw {
   using F = LinkFmt<P, R>;
   uint32_t w[F::K * F::E / 4];
 };
-
-template <int P, int R>
-__device__ inline void link_load_raw(const void* links, int mu, int p, int h, int Nh, LinkRaw<P, R>& r) {
-  using F = LinkFmt<P, R>;
-  const char* b = static_cast<const char*>(links) + ((static_cast<size_t>(mu) * 2 + p) * F::K * Nh + h) * F::E;
-#pragma unroll
-  for (int k = 0; k < F::K; ++k) {
-    const char* a = b + static_cast<size_t>(k) * Nh * F::E;
-    if constexpr (F::E == 16) {
-      const uint4 v = *reinterpret_cast<const uint4*>(a);
-      r.w[4 * k] = v.x;
-      r.w[4 * k + 1] = v.y;
-      r.w[4 * k + 2] = v.z;
-      r.w[4 * k + 3] = v.w;
-    } else if constexpr (F::E == 8) {
-      const uint2 v = *reinterpret_cast<const uint2*>(a);
-      r.w[2 * k] = v.x;
-      r.w[2 * k + 1] = v.y;
-    } else {
-      r.w[k] = *reinterpret_cast<const uint32_t*>(a);
-    }
-  }
-}
 
 template <int P, int R>
 __device__ inline void link_unpack(const LinkRaw<P, R>& r, Cx<typename Prec<P>::real> (*u)[3]) {
