@@ -602,13 +602,16 @@ __global__ __launch_bounds__(256) void rotate_kernel(int Nh, int K, int k, char*
 
 // Waves of a dot_kernel block: the tiles of 16 modes in equal groups of at most
 // eight (each group reads the batch again).  A wave loads as long for a part of a
-// tile as for a whole one, so 3, 5 and 6 waves have kernels of their own: 24^3x64,
-// FP64, 4 vectors, 33 modes 1238 us with 4 waves, 1056 with 3; 130 modes 4310 with
-// twice 7, 3692 with twice 5; 12 vectors, 80 modes 3490 with 7, 3316 with 5 (F16 12
-// vectors, 72 modes, where the matrix instructions weigh more: 3210 and 3360).
-int dot_waves(int ell) {
-  const int tiles = (ell + 15) / 16, groups = (tiles + 7) / 8;
-  return (tiles + groups - 1) / groups;
+// tile as for a whole one, so up to 8 vectors take 5 or 6 waves where those do
+// (24^3x64, FP64, 4 vectors, 130 modes: twice 7 waves 4310 us, twice 5 3692; the
+// projection at 14x18x10x34, FP32, 5 vectors, 7% less).  With two column tiles the
+// matrix instructions weigh more and 7 waves are ahead (F16, 12 vectors, 72 modes,
+// 24^3x64: 3210 against 3360 us), and three waves, though 14% ahead of four alone,
+// leave less of the basis in the Infinity Cache for the second reading (that
+// projection, 37 modes: 290 us with four, 300 with three).
+int dot_waves(int ell, int R) {
+  const int tiles = (ell + 15) / 16, groups = (tiles + 7) / 8, nw = (tiles + groups - 1) / groups;
+  return nw == 3 ? 4 : R > 8 && (nw == 5 || nw == 6) ? 7 : nw;
 }
 
 // Batches up to this take dot_small_kernel.  With two vectors dot_kernel is ahead by
@@ -637,7 +640,7 @@ int dot_blocks(const ovl_geom* g, int ell, int R) {
     return static_cast<int>(std::max(1L, std::min((units + 3) / 4, 256L * (16 / nw) / groups)));
   }
   const long units = 24L * ((g->geo.Nh + PJ_TILE - 1) / PJ_TILE);
-  const int nw = dot_waves(ell), groups = (ell + 16 * nw - 1) / (16 * nw);
+  const int nw = dot_waves(ell, R), groups = (ell + 16 * nw - 1) / (16 * nw);
   const long held = 256L * ((160 << 10) / ((nw * 16 + 2 * OVL_MAX_RHS) * PJ_PAD * 16));
   return static_cast<int>(std::max(1L, std::min((units + 3) / 4, held / groups)));
 }
@@ -651,8 +654,9 @@ void dot_go(const ovl_geom* g, const void* V, int ell, const void* psi, int R, d
 
 template <int P, int NT, int NW = 8>
 void dot_mt(const ovl_geom* g, const void* V, int ell, const void* psi, int R, double2* part, int G, hipStream_t s) {
+  constexpr int next = NW == 4 ? 2 : NT == 2 && NW == 7 ? 4 : NW - 1;  // the counts that dot_waves gives
   if constexpr (NW > 1)
-    if (dot_waves(ell) < NW) return dot_mt<P, NT, NW - 1>(g, V, ell, psi, R, part, G, s);
+    if (dot_waves(ell, R) < NW) return dot_mt<P, NT, next>(g, V, ell, psi, R, part, G, s);
   dot_go<P, NW, NT>(g, V, ell, psi, R, part, G, s);
 }
 
