@@ -84,10 +84,14 @@ __device__ inline Cx<float> rounded_mul(Cx<float> u, Cx<float> s) {
 }
 
 // out = U s (DAG: U^dag s) for the weight gradient, whose FP32 sums are handed
-// out in FP64: each complex product is rounded before it is added, and the
-// order within the products is the one that the first version of the kernel
-// compiled to (it differs in columns 0 and 2 of a rebuilt third row), so the
-// gradients are the same to the last bit and training runs repeat.
+// out in FP64: each complex product is rounded before it is added.  Which of a
+// part's two products is rounded and which fused (columns 0 and 2 of a rebuilt
+// third row have it the other way round) is a choice without a reason in the
+// arithmetic: it is the one that gradients and trained weights of earlier builds
+// were made with, and is kept so that they repeat.  The blocks' FP32 sums are the
+// same to the last bit; the FP64 sum over the 256 blocks runs in another order
+// than in those builds, which changed none of 3600 gradient entries (8 shapes from
+// 4^4 to 24^3x64).  It costs six instructions per product where colour_add takes four.
 template <int R, bool DAG>
 __device__ inline void colour_mul12(const Cx<float> (*u)[3], const Cx<float>* s, Cx<float>* out) {
 #pragma unroll
@@ -199,8 +203,8 @@ __global__ __launch_bounds__(256) void ptc_forward_kernel(Geo g, const void* lin
 // Sums v[0..N) over the wave, the values dealt out over the lanes: every step
 // halves the lanes that share a value and the values a lane keeps, N + N/2 +
 // ... exchanges instead of 6 N, with the pairs of a butterfly (so its sums, to
-// the last bit).  On return v[0..n) are the sums of the values
-// base + 0..n; returns n (compile-time) and sets base.
+// the last bit).  On return v[0..dealt(N)) are the sums of the values
+// base + 0..dealt(N) - 1 of this lane.
 template <int N, int O>
 __device__ inline void wave_deal(float* v, int lane, int& base) {
   if constexpr (O >= 1) {

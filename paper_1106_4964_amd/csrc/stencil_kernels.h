@@ -410,7 +410,7 @@ __device__ inline void keep(T& x) {
 // hops one after the other takes 48.  (g's colour products accumulated onto f,
 // and g - f = (f + g) - 2 f, would save 12 more, but round once more: H_w in
 // FP32 6.21e-8 from the 64-bit result against 5.96e-8, and at F16 storage 4.66
-// of 10^4 stored reals other than the exact ones' rounding, where this has 4.23
+// of 10^4 stored reals other than the exact ones' rounding, where this has 4.24
 // and the hops added one after the other 4.34.)
 template <int P, int R, int MU, int KR, bool SPLIT>
 __device__ inline void hops(const StencilArgs& A, const char* in, int p, int h, int x, int y, int z, int t,
