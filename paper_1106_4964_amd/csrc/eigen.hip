@@ -16,8 +16,8 @@
 //    Stops when the ell pairs with smallest |theta| have
 //    ||H_w v - theta v|| <= tol * lam_max.
 //
-// Dense m x m problems (Gram and Rayleigh-Ritz matrices, the Lanczos
-// tridiagonal) are solved on the host by cyclic complex Jacobi rotations.
+// Dense m x m problems (Gram and Rayleigh-Ritz matrices) are solved on the host
+// by cyclic complex Jacobi rotations, the bound's tridiagonal by shifted QR.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
